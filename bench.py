@@ -62,7 +62,8 @@ TRAFFIC_FILE = os.path.join(PROFILE_DIR, "k_cheb_step_qb_cube64_hbm_traffic.txt"
 # Sources that decide what one launch of the dominant kernel reads and writes:
 # the kernel bodies, their launch wrappers, the shared structures, and the
 # assembly that lays out the matrix (row order, slots, packed indices).
-DIGEST_SOURCES = ["kernels.h", "common.h", "ops.hip", "ops.h", "assemble.hip", "mesh_host.cpp", "mesh_host.h"]
+DIGEST_SOURCES = ["kernels.h", "common.h", "ops.hip", "ops.h", "dispatch.h", "cheb_step.hip", "assemble.hip",
+                  "mesh_host.cpp", "mesh_host.h"]
 
 
 def kernel_source_digest():

@@ -425,20 +425,22 @@ __device__ __forceinline__ void sell_row_il(const SellIdx& ix, const TM* __restr
   else sell_row_il_impl<T, W, G, TM, 0>(ix, r, vals, x, off, acc);
 }
 
-// B rows (pressure vertex): acc[r] = sum_j sum_c B^c_j u[col_j][r][c]
-// (entries walked two at a time to keep more loads in flight)
-template <typename T, int D, int NRB, int F>
+// B rows (pressure vertex): acc[r] = sum_j sum_c B^c_j u[col_j][r][c] over the
+// slots j = sub, sub + E, ... of the row (E lanes share a row; E = 1: all),
+// walked U at a time to keep more loads in flight (U = 4 on split rows; two
+// where whole rows already fill the chip: 49 us against 55 on 274,625 rows,
+// FP32).
+template <typename T, int D, int NRB, int E, int F>
 __device__ __forceinline__ void sell_row_B_impl(const SellIdx& ix, const SliceRef& rf, const T* __restrict__ vals,
-                                                const T* __restrict__ u, T (&acc)[NRB]) {
-  constexpr int U = 2;
-  int j = 0;
-  for (; j + U <= rf.width; j += U) {
+                                                const T* __restrict__ u, int sub, T (&acc)[NRB]) {
+  auto group = [&](auto Uc, int j) {
+    constexpr int U = decltype(Uc)::value;
     int32_t c[U];
     T b[U][D], x[U][D * NRB];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      const int64_t k = rf.beg + 64 * (j + q);
-      c[q] = sell_col_f<F>(ix, rf, j + q);
+      const int64_t k = rf.beg + 64 * (j + E * q);
+      c[q] = sell_col_f<F>(ix, rf, j + E * q);
 #pragma unroll
       for (int d = 0; d < D; ++d) b[q][d] = __builtin_nontemporal_load(vals + k * D + d);
     }
@@ -452,28 +454,27 @@ __device__ __forceinline__ void sell_row_B_impl(const SellIdx& ix, const SliceRe
       for (int r = 0; r < NRB; ++r)
 #pragma unroll
         for (int d = 0; d < D; ++d) acc[r] = fma(b[q][d], x[q][r * D + d], acc[r]);
-  }
-  for (; j < rf.width; ++j) {
-    const int64_t k = rf.beg + 64 * j;
-    const int32_t c = sell_col_f<F>(ix, rf, j);
-    T b[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) b[d] = __builtin_nontemporal_load(vals + k * D + d);
-    const T* up = u + (int64_t)c * (D * NRB);
-#pragma unroll
-    for (int r = 0; r < NRB; ++r)
-#pragma unroll
-      for (int d = 0; d < D; ++d) acc[r] = fma(b[d], up[r * D + d], acc[r]);
-  }
+  };
+  constexpr int U = E > 1 && NRB <= 2 ? 4 : 2;
+  int j = sub;
+  for (; j + E * (U - 1) < rf.width; j += E * U) group(std::integral_constant<int, U>{}, j);
+  for (; j < rf.width; j += E) group(std::integral_constant<int, 1>{}, j);
 }
 
-template <typename T, int D, int NRB>
+template <typename T, int D, int NRB, int E>
 __device__ __forceinline__ void sell_row_B(const SellIdx& ix, const T* __restrict__ vals, const T* __restrict__ u,
-                                           int64_t row, T (&acc)[NRB]) {
+                                           int64_t row, int sub, T (&acc)[NRB]) {
   const SliceRef rf = slice_ref(ix, row);
-  if (rf.af) sell_row_B_impl<T, D, NRB, 2>(ix, rf, vals, u, acc);
-  else if (rf.pk) sell_row_B_impl<T, D, NRB, 1>(ix, rf, vals, u, acc);
-  else sell_row_B_impl<T, D, NRB, 0>(ix, rf, vals, u, acc);
+  if (rf.af) sell_row_B_impl<T, D, NRB, E, 2>(ix, rf, vals, u, sub, acc);
+  else if (rf.pk) sell_row_B_impl<T, D, NRB, E, 1>(ix, rf, vals, u, sub, acc);
+  else sell_row_B_impl<T, D, NRB, E, 0>(ix, rf, vals, u, sub, acc);
+  if constexpr (E > 1) {
+    // the lanes of a row exchange their sums; all of them end with the same bits
+#pragma unroll
+    for (int o = E / 2; o >= 1; o /= 2)
+#pragma unroll
+      for (int r = 0; r < NRB; ++r) acc[r] += __shfl_xor(acc[r], o);
+  }
 }
 
 // value plane d (runtime, d < D) of a small register array
@@ -1336,20 +1337,29 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step_qb(int64_t nrows, SellIdx 
 
 // ------------------------------------------------------------- B and B^T
 
-// p = a * (B u) + b * pin
-template <typename T, int D, int NRB>
+// p = a * (B u) + b * pin, E lanes per pressure row.  A pressure row has some
+// 60 (P2/P1) or 65-240 (P3/P2) entries of D values, and meshes of a few tens
+// of cells have few such rows: one lane per row then leaves most of the chip
+// idle behind a serial chain of gathers (2.2 wavefronts per CU at 35,937
+// rows).  E by the launcher (bmul.hip).  3D P2/P1, one right-hand side, FP32
+// / FP64, one lane per row before and now: 1,000 rows 10.2 / 11.2 -> 4.5 /
+// 5.8 us, 15,625 rows 13.7 / 21.0 -> 7.1 / 11.2 us, 35,937 rows 24.6 / 29.8
+// -> 14.6 / 24.6 us, 68,921 rows 29.5 / 46.7 -> 20.2 / 41.0 us.
+template <typename T, int D, int NRB, int E>
 __global__ __launch_bounds__(kBlock) void k_B(int64_t nrows, SellIdx ix, const T* __restrict__ vals,
                                               const T* __restrict__ u, T* pout, T a, const T* pin, T b) {
-  XCD_ROWS(row, nrows, ix.rperm) {
+  XCD_ROWS_G(row, sub, nrows, E, ix.rperm) {
     T acc[NRB];
 #pragma unroll
     for (int r = 0; r < NRB; ++r) acc[r] = 0;
-    sell_row_B<T, D, NRB>(ix, vals, u, row, acc);
-    T pi[NRB];  // pin may alias pout
+    sell_row_B<T, D, NRB, E>(ix, vals, u, row, sub, acc);
+    // pin may alias pout: a lane alone reads and then writes its right-hand sides
+    T pi[NRB];
 #pragma unroll
-    for (int r = 0; r < NRB; ++r) pi[r] = b != T(0) ? pin[row * NRB + r] : T(0);
+    for (int r = 0; r < NRB; ++r) pi[r] = (b != T(0) && r % E == sub) ? pin[row * NRB + r] : T(0);
 #pragma unroll
-    for (int r = 0; r < NRB; ++r) pout[row * NRB + r] = fma(b, pi[r], a * acc[r]);
+    for (int r = 0; r < NRB; ++r)
+      if (r % E == sub) pout[row * NRB + r] = fma(b, pi[r], a * acc[r]);
   }
 }
 
@@ -1716,7 +1726,20 @@ __global__ __launch_bounds__(kBlock) void k_rhs_p(int64_t n_p1, int64_t n_p2, co
   }
 }
 
-// Gradient pieces of the adjoint (FP64, CSR over all P2 nodes):
+// Gradient pieces of the adjoint (FP64, CSR over all P2 nodes).  kCsrLanes
+// lanes walk a row together, so that its columns and values are read in
+// consecutive words, and add their sums by lane exchanges (one lane per row
+// took 491 and 591 us on the 531,441 rows of a 40^3 mesh).
+constexpr int kCsrLanes = 16;
+
+template <int W>
+__device__ __forceinline__ void csr_lanes_sum(double (&acc)[W]) {
+#pragma unroll
+  for (int o = kCsrLanes / 2; o >= 1; o /= 2)
+#pragma unroll
+    for (int w = 0; w < W; ++w) acc[w] += __shfl_xor(acc[w], o);
+}
+
 // dJdf[r][d][nat] = sum_k M[k] lam[int(col_k)]   (zero outside the interior)
 template <int D, int NRB>
 __global__ __launch_bounds__(kBlock) void k_adj_dJdf(int64_t n_p2, const int32_t* __restrict__ nat2int,
@@ -1724,21 +1747,24 @@ __global__ __launch_bounds__(kBlock) void k_adj_dJdf(int64_t n_p2, const int32_t
                                                      const double* __restrict__ M, const double* __restrict__ lam,
                                                      double* __restrict__ out) {
   constexpr int W = D * NRB;
-  GRID_STRIDE_ROWS(nat, n_p2) {
+  GRID_STRIDE_ROWS_G(nat, sub, n_p2, kCsrLanes) {
     double acc[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) acc[w] = 0;
-    for (int64_t k = rp[nat]; k < rp[nat + 1]; ++k) {
+    const int32_t end = rp[nat + 1];
+    for (int32_t k = rp[nat] + sub; k < end; k += kCsrLanes) {
       const int64_t c = nat2int[cols[k]];
       if (c < 0) continue;
       const double m = M[k];
 #pragma unroll
       for (int w = 0; w < W; ++w) acc[w] += m * lam[c * W + w];
     }
+    csr_lanes_sum<W>(acc);
 #pragma unroll
     for (int r = 0; r < NRB; ++r)
 #pragma unroll
-      for (int d = 0; d < D; ++d) out[((int64_t)r * D + d) * n_p2 + nat] = acc[r * D + d];
+      for (int d = 0; d < D; ++d)
+        if ((r * D + d) % kCsrLanes == sub) out[((int64_t)r * D + d) * n_p2 + nat] = acc[r * D + d];
   }
 }
 
@@ -1753,12 +1779,13 @@ __global__ __launch_bounds__(kBlock) void k_adj_dJdmu(int64_t n_int, int64_t n_p
   double part[NRB];
 #pragma unroll
   for (int r = 0; r < NRB; ++r) part[r] = 0;
-  GRID_STRIDE_ROWS(row, n_int) {
+  GRID_STRIDE_ROWS_G(row, sub, n_int, kCsrLanes) {
     const int64_t nat = int2nat[row];
     double acc[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) acc[w] = 0;
-    for (int64_t k = rp[nat]; k < rp[nat + 1]; ++k) {
+    const int32_t end = rp[nat + 1];
+    for (int32_t k = rp[nat] + sub; k < end; k += kCsrLanes) {
       const int64_t c = cols[k];
       const double l = L[k];
 #pragma unroll
@@ -1767,10 +1794,11 @@ __global__ __launch_bounds__(kBlock) void k_adj_dJdmu(int64_t n_int, int64_t n_p
         for (int d = 0; d < D; ++d) {
           double t = l * u[((int64_t)r * D + d) * n_p2 + c];
           if (Dg)  // strain form: the viscous matrix is L + D
-            for (int b = 0; b < D; ++b) t += Dg[k * D * D + d * D + b] * u[((int64_t)r * D + b) * n_p2 + c];
+            for (int b = 0; b < D; ++b) t += Dg[(int64_t)k * D * D + d * D + b] * u[((int64_t)r * D + b) * n_p2 + c];
           acc[r * D + d] += t;
         }
     }
+    // every lane keeps its own share of the row's product with lam
 #pragma unroll
     for (int r = 0; r < NRB; ++r)
 #pragma unroll

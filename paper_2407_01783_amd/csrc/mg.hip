@@ -195,23 +195,35 @@ T* wsp(stokes_ctx* c, const std::string& name, int64_t n) {
 
 
 // y[row][w] (+)= sum_k vals[k] x[cols[k]][w] over CSR rows (grid transfers
-// of the velocity multigrid, W interleaved components per node)
-template <typename T, int W, int ACC>
+// of the velocity multigrid, W interleaved components per node), E lanes per
+// row: they read consecutive entries and add their sums by lane exchanges.
+// Restriction rows have some 30-100 entries and there are few of them (16
+// lanes: 29,791 rows 43 -> 8.7 us, 343 rows 30 -> 5.8 us, FP32), prolongation
+// rows up to ten (2 lanes: 250,047 rows 7.8 -> 7.0 us).
+template <typename T, int W, int ACC, int E>
 __global__ __launch_bounds__(kBlock) void k_csr_w(int64_t nrows, const int32_t* __restrict__ rp,
                                                   const int32_t* __restrict__ cols, const T* __restrict__ vals,
                                                   const T* __restrict__ x, T* __restrict__ y) {
-  GRID_STRIDE_ROWS(row, nrows) {
+  GRID_STRIDE_ROWS_G(row, sub, nrows, E) {
     T acc[W];
 #pragma unroll
-    for (int w = 0; w < W; ++w) acc[w] = ACC ? y[row * W + w] : T(0);
-    for (int32_t k = rp[row]; k < rp[row + 1]; ++k) {
+    for (int w = 0; w < W; ++w) acc[w] = 0;
+    const int32_t end = rp[row + 1];
+    for (int32_t k = rp[row] + sub; k < end; k += E) {
       const T v = vals[k];
       const T* xp = x + (int64_t)cols[k] * W;
 #pragma unroll
       for (int w = 0; w < W; ++w) acc[w] = fma(v, xp[w], acc[w]);
     }
+    if constexpr (E > 1) {
 #pragma unroll
-    for (int w = 0; w < W; ++w) y[row * W + w] = acc[w];
+      for (int o = E / 2; o >= 1; o /= 2)
+#pragma unroll
+        for (int w = 0; w < W; ++w) acc[w] += __shfl_xor(acc[w], o);
+    }
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      if (w % E == sub) y[row * W + w] = ACC ? y[row * W + w] + acc[w] : acc[w];
   }
 }
 
@@ -560,6 +572,11 @@ void build_vmg(stokes_ctx* c) {
       for (int d = 0; d < D; ++d) m.vcoords[g * D + d] = fm.vcoords[fid * D + d];
     }
     assemble_p2_level(c, m, *L);
+    // lanes per row: coarse levels have at most an eighth of the fine rows, too
+    // few to hide a row's chain of gathers behind other rows.  FP32, 3D, one
+    // right-hand side, one lane / 4 / 8 per row: 29,791 rows 13.2 / 8.5 / 11.3
+    // us per product, 3,375 rows 12.2 / 6.2 / 5.5 us.
+    L->S.es = L->S.nrows < (int64_t(1) << 14) ? 8 : 4;
     HostCsr P, R;
     std::vector<double> pv;
     p2_prolongation(D, nf, fine_nat, P, pv);
@@ -659,7 +676,7 @@ void vel_vcycle(stokes_ctx* c, int W, const T* r, T* e, int lv) {
   ops::spmv<T>(c, S, vals, W, e, t, (T)-1, r, (T)1);     // t = r - A e
   dispatch_w_mg(W, [&](auto Wc) {
     constexpr int WW = decltype(Wc)::value;
-    hipLaunchKernelGGL((k_csr_w<T, WW, 0>), dim3(ops::grid_for(C.nrows)), dim3(kBlock), 0, c->stream, C.nrows,
+    hipLaunchKernelGGL((k_csr_w<T, WW, 0, 16>), dim3(ops::grid_full(C.nrows * 16)), dim3(kBlock), 0, c->stream, C.nrows,
                        C.R.rowptr.as<int32_t>(), C.R.cols.as<int32_t>(), ops::pick<T>(C.rv64, C.rv32), (const T*)t, rc);
   });
   ops::check_launch();
@@ -668,7 +685,7 @@ void vel_vcycle(stokes_ctx* c, int W, const T* r, T* e, int lv) {
   vel_vcycle<T>(c, W, rc, ec, lv + 1);
   dispatch_w_mg(W, [&](auto Wc) {
     constexpr int WW = decltype(Wc)::value;
-    hipLaunchKernelGGL((k_csr_w<T, WW, 1>), dim3(ops::grid_for(nr)), dim3(kBlock), 0, c->stream, nr,
+    hipLaunchKernelGGL((k_csr_w<T, WW, 1, 2>), dim3(ops::grid_full(nr * 2)), dim3(kBlock), 0, c->stream, nr,
                        C.P.rowptr.as<int32_t>(), C.P.cols.as<int32_t>(), ops::pick<T>(C.pv64, C.pv32), (const T*)ec, e);
   });
   ops::check_launch();

@@ -34,6 +34,7 @@ void lanczos_bounds(stokes_ctx* c, const Sell& S, const double* vals, const doub
 namespace ops {
 
 int grid_for(int64_t rows);
+int grid_full(int64_t rows);  // one row (group) per thread, a multiple of 8 workgroups
 // lanes per row of the velocity-row kernels, autotuned once per (W, precision)
 void ensure_lanes(stokes_ctx* c, int W, bool f32);
 bool prof_begin(stokes_ctx* c, const Sell* S, const void* vals, const void* avals);

@@ -4,8 +4,7 @@
 #include <string>
 #include <type_traits>
 
-#include "kernels.h"
-#include "ops.h"
+#include "dispatch.h"
 
 namespace stokes {
 namespace ops {
@@ -94,149 +93,6 @@ void phase_end(stokes_ctx* c, int k) noexcept {
 }
 
 namespace {
-
-template <int V>
-using IC = std::integral_constant<int, V>;
-
-// W in {1,2,3,4,6,8,12,16,24}
-template <class F>
-void dispatch_w(int W, F&& f) {
-  switch (W) {
-    case 1: f(IC<1>{}); break;
-    case 2: f(IC<2>{}); break;
-    case 3: f(IC<3>{}); break;
-    case 4: f(IC<4>{}); break;
-    case 6: f(IC<6>{}); break;
-    case 8: f(IC<8>{}); break;
-    case 12: f(IC<12>{}); break;
-    case 16: f(IC<16>{}); break;
-    case 24: f(IC<24>{}); break;
-    default: throw Error(STOKES_ERR_UNSUPPORTED, "unsupported vector width " + std::to_string(W));
-  }
-}
-
-// dim in {2,3}, nrb in {1,2,4,8}
-template <class F>
-void dispatch_dn(int D, int NRB, F&& f) {
-  auto inner = [&](auto Dc) {
-    switch (NRB) {
-      case 1: f(Dc, IC<1>{}); break;
-      case 2: f(Dc, IC<2>{}); break;
-      case 4: f(Dc, IC<4>{}); break;
-      case 8: f(Dc, IC<8>{}); break;
-      default: throw Error(STOKES_ERR_UNSUPPORTED, "unsupported batch " + std::to_string(NRB));
-    }
-  };
-  if (D == 3) inner(IC<3>{});
-  else if (D == 2) inner(IC<2>{});
-  else throw Error(STOKES_ERR_UNSUPPORTED, "dim");
-}
-
-inline double* partials(stokes_ctx* c) { return c->red.partials.as<double>(); }
-
-// Lanes per row G of the velocity-row kernels: the largest of 8, 4, 2 not
-// above the request that divides W (the compiled variants).
-template <int WW, class F>
-void with_g(int G, F&& f) {
-  if constexpr (WW % 8 == 0) {
-    if (G >= 8) return f(IC<8>{});
-  }
-  if constexpr (WW % 4 == 0) {
-    if (G >= 4) return f(IC<4>{});
-  }
-  if constexpr (WW % 2 == 0) {
-    if (G >= 2) return f(IC<2>{});
-  }
-  f(IC<1>{});
-}
-
-// Entry-split lanes E of a scalar operator (Sell::es, tuned per multigrid
-// level); compiled for the pressure widths W in {1, 2, 4, 8}.  Returns false
-// (nothing launched) for other E or W.
-template <int WW, class F>
-bool with_e(int E, F&& f) {
-  if constexpr (WW == 1 || WW == 2 || WW == 4 || WW == 8) {
-    switch (E) {
-      case 2: f(IC<2>{}); return true;
-      case 4: f(IC<4>{}); return true;
-      case 8: f(IC<8>{}); return true;
-      case 16: f(IC<16>{}); return true;
-      default: return false;
-    }
-  } else {
-    (void)E;
-    (void)f;
-    return false;
-  }
-}
-
-// Index of the interleaved copies of the velocity pattern (iw slots per group).
-SellIdx vel_il_idx(stokes_ctx* c, int W, int iw) {
-  SellIdx ix = c->sA.idx(W);
-  ix.cdel = (iw == 8 ? c->cdel_i8 : c->cdel_i).as<const uint8_t>();
-  ix.cols = (iw == 8 ? c->cols_i8 : c->cols_i).as<const int32_t>();
-  if (!c->vel_af) ix.cmeta = nullptr;  // read the packed offsets of affine slots too
-  return ix;
-}
-
-// Before tuning: the largest G leaving each lane at least 3 components.
-int heuristic_lanes(int W) {
-  for (int g : {8, 4, 2})
-    if (W % g == 0 && W / g >= 3) return g;
-  return 1;
-}
-
-int lanes_w(stokes_ctx* c, int W, bool f32) {
-  if (c->force_lanes > 0) return c->force_lanes;
-  const auto it = c->lanes.find(W * 2 + (f32 ? 1 : 0));
-  return it != c->lanes.end() ? it->second : heuristic_lanes(W);
-}
-
-// B^T rows have their own tuned G (key offset kBtKey)
-constexpr int kBtKey = 1 << 20;
-int lanes_bt(stokes_ctx* c, int W, bool f32) {
-  if (c->force_lanes > 0) return c->force_lanes;
-  const auto it = c->lanes.find(kBtKey + W * 2 + (f32 ? 1 : 0));
-  return it != c->lanes.end() ? it->second : lanes_w(c, W, f32);
-}
-
-// the bfloat16-direction Chebyshev kernels too (key offset kQbKey)
-constexpr int kQbKey = 2 << 20;
-int lanes_qb(stokes_ctx* c, int W) {
-  if (c->force_lanes > 0) return c->force_lanes;
-  const auto it = c->lanes.find(kQbKey + W * 2 + 1);
-  return it != c->lanes.end() ? it->second : lanes_w(c, W, true);
-}
-
-// velocity-row operators use the tuned G; the pressure operators one lane per row
-int lanes_op(stokes_ctx* c, const Sell* S, int W, bool f32) {
-  if (S == &c->sBt) return lanes_bt(c, W, f32);
-  return S == &c->sA ? lanes_w(c, W, f32) : 1;
-}
-
-int lanes_rows(stokes_ctx* c, int64_t nrows, int W, bool f32) {
-  return nrows == c->n_int ? lanes_w(c, W, f32) : 1;
-}
-
-template <int NS>
-void finish(stokes_ctx* c, int64_t rows, int kind, int W, Scalars* sc, int cps, int nsys, int first, double* res) {
-  hipLaunchKernelGGL((k_finish<NS>), dim3(1), dim3(kBlock), 0, c->stream, (const double*)partials(c), grid_for(rows),
-                     kind, W, sc, cps, nsys, first, res);
-}
-
-template <class T> const DevBuf& bvals(stokes_ctx* c);
-template <> const DevBuf& bvals<double>(stokes_ctx* c) { return c->B64; }
-template <> const DevBuf& bvals<float>(stokes_ctx* c) { return c->B32; }
-template <class T> const DevBuf& btvals(stokes_ctx* c);
-template <> const DevBuf& btvals<double>(stokes_ctx* c) { return c->Bt64; }
-template <> const DevBuf& btvals<float>(stokes_ctx* c) { return c->Bt32; }
-template <class T> const DevBuf& avals(stokes_ctx* c);
-template <> const DevBuf& avals<double>(stokes_ctx* c) { return c->A64; }
-template <> const DevBuf& avals<float>(stokes_ctx* c) { return c->A32; }
-
-}  // namespace
-
-namespace {
 // S = ms * (stored values); ms is folded into the product's coefficient
 template <class T, class TM>
 void spmv_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, int W, const T* x, T* y, T a, const T* yin, T b) {
@@ -258,7 +114,7 @@ void spmv_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, int W, const 
         return;
       }
     }
-    if (S.es > 1 && with_e<WW>(S.es, [&](auto Ec) {
+    if (S.es > 1 && with_e<WW, std::is_same<T, TM>::value>(S.es, [&](auto Ec) {
           constexpr int EE = decltype(Ec)::value;
           hipLaunchKernelGGL((k_spmv_es<T, WW, EE, TM>), dim3(grid_full(S.nrows * EE)), dim3(kBlock), 0, c->stream,
                              S.nrows, S.idx(WW), vals, x, y, (T)(a * ms), yin, b);
@@ -285,20 +141,6 @@ void spmv(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* x, T* y, 
 void spmv_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* x, float* y, float a,
              const float* yin, float b) {
   spmv_impl<float, _Float16>(c, S, vals, ms, W, x, y, a, yin, b);
-}
-
-template <class T>
-void Bmul(stokes_ctx* c, int nrb, const T* u, T* p, T a, const T* pin, T b) {
-  const Sell& S = c->sB;
-  dispatch_dn(c->dim, nrb, [&](auto Dc, auto Nc) {
-    constexpr int D = decltype(Dc)::value, N = decltype(Nc)::value;
-    hipLaunchKernelGGL((k_B<T, D, N>), dim3(grid_full(S.nrows)), dim3(kBlock), 0, c->stream, S.nrows,
-                       S.idx(), bvals<T>(c).template as<T>(), u, p, a, pin, b);
-  });
-  check_launch();
-  // B (dim planes), u gathered, p written (and pin read)
-  count_bytes(c, op_bytes(S, sizeof(T)) + double(S.ncols) * c->dim * nrb * sizeof(T) +
-                     double(S.nrows) * nrb * sizeof(T) * (pin ? 2 : 1));
 }
 
 template <class T>
@@ -449,311 +291,6 @@ void axpy_sys(stokes_ctx* c, int64_t n, int W, int cps, const double* coef, doub
   hipLaunchKernelGGL((k_axpy_sys<T>), dim3(grid_for(n)), dim3(kBlock), 0, c->stream, n, W, cps, coef, scale, v, y);
   check_launch();
   count_bytes(c, double(n) * sizeof(T) * 3);
-}
-
-template <class T>
-void cg_spmv(stokes_ctx* c, int64_t nrows, const Sell* S, const T* vals, int W, const T* z, const T* extra, T* q,
-             T* p, Scalars* sc, int cps, int nsys) {
-  const int G = S ? lanes_op(c, S, W, std::is_same<T, float>::value) : 1;
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      hipLaunchKernelGGL((k_cg_spmv<T, WW, GG>), dim3(grid_for(nrows * GG)), dim3(kBlock), 0, c->stream, nrows,
-                         S ? S->idx(WW) : SellIdx{}, vals, z,
-                         extra, q, p, sc, cps, nsys, partials(c));
-      finish<WW>(c, nrows * GG, FIN_ALPHA, WW, sc, cps, nsys, 0, nullptr);
-    });
-  });
-  check_launch();
-  // operator and z gathered (z streamed without one), q and p read and written (extra read)
-  count_bytes(c, (S ? op_bytes(*S, sizeof(T)) + double(S->ncols) * W * sizeof(T) : 0) +
-                     double(nrows) * W * sizeof(T) * (4 + (extra ? 1 : 0) + (S ? 0 : 1)));
-}
-
-template <class T>
-void cg_update(stokes_ctx* c, int64_t nrows, int W, int prec, T* x, T* r, const T* p, const T* q, const T* dinv,
-               T theta_inv, T* d0, T* z, Scalars* sc, int cps, int nsys) {
-  const int G = lanes_rows(c, nrows, W, std::is_same<T, float>::value);
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      const int nb = grid_for(nrows * GG);
-      if (prec == 2) {
-        hipLaunchKernelGGL((k_cg_update<T, WW, 2, GG>), dim3(nb), dim3(kBlock), 0, c->stream, nrows, x, r, p, q, dinv,
-                           theta_inv, d0, z, sc, cps, nsys, partials(c));
-        finish<WW>(c, nrows * GG, FIN_RR, WW, sc, cps, nsys, 0, nullptr);
-      } else if (prec == 0) {
-        hipLaunchKernelGGL((k_cg_update<T, WW, 0, GG>), dim3(nb), dim3(kBlock), 0, c->stream, nrows, x, r, p, q, dinv,
-                           theta_inv, d0, z, sc, cps, nsys, partials(c));
-        finish<WW>(c, nrows * GG, FIN_RR, WW, sc, cps, nsys, 0, nullptr);
-      } else {
-        hipLaunchKernelGGL((k_cg_update<T, WW, 1, GG>), dim3(nb), dim3(kBlock), 0, c->stream, nrows, x, r, p, q, dinv,
-                           theta_inv, d0, z, sc, cps, nsys, partials(c));
-        finish<2 * WW>(c, nrows * GG, FIN_RR_RHO, WW, sc, cps, nsys, 0, nullptr);
-      }
-    });
-  });
-  check_launch();
-  // x, r read and written, p, q read; dinv; d0 and z (or z) written
-  count_bytes(c, double(nrows) * (W * sizeof(T) * (6 + (prec == 0 ? 2 : prec == 1 ? 1 : 0)) +
-                                  (prec == 2 ? 0 : sizeof(T))));
-}
-
-template <class T>
-void cheb_init(stokes_ctx* c, int64_t nrows, int W, const T* r, const T* dinv, T theta_inv, T* d0, T* z) {
-  const int G = lanes_rows(c, nrows, W, std::is_same<T, float>::value);
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      hipLaunchKernelGGL((k_cheb_init<T, WW, GG>), dim3(grid_for(nrows * GG)), dim3(kBlock), 0, c->stream, nrows, r,
-                         dinv, theta_inv, d0, z);
-    });
-  });
-  check_launch();
-  count_bytes(c, double(nrows) * (W * sizeof(T) * 3 + sizeof(T)));
-}
-
-namespace {
-template <class T, class TM>
-void cheb_first_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, const TM* scaled, int W, const T* r,
-                     const T* dinv, T theta_inv, T* d1, T* res, T* z, T c1, T c2, int accumulate) {
-  const int G = lanes_op(c, &S, W, std::is_same<T, float>::value);
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    if (!scaled && S.es > 1 && with_e<WW>(S.es, [&](auto Ec) {
-          constexpr int EE = decltype(Ec)::value;
-          auto kern = accumulate ? k_cheb_first_es<T, WW, 1, EE, TM> : k_cheb_first_es<T, WW, 0, EE, TM>;
-          hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * EE)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), vals,
-                             ms, r, dinv, theta_inv, d1, res, z, c1, c2);
-        }))
-      return;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      const int nb = grid_full(S.nrows * GG);
-      auto go = [&](auto kern, const TM* v) {
-        hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), v, ms, r, dinv, theta_inv,
-                           d1, res, z, c1, c2);
-      };
-      if (scaled) {
-        if (accumulate) go(k_cheb_first<T, WW, 1, GG, 1, TM>, scaled);
-        else go(k_cheb_first<T, WW, 0, GG, 1, TM>, scaled);
-      } else {
-        if (accumulate) go(k_cheb_first<T, WW, 1, GG, 0, TM>, vals);
-        else go(k_cheb_first<T, WW, 0, GG, 0, TM>, vals);
-      }
-    });
-  });
-  check_launch();
-  // operator, r gathered (and dinv with the unscaled one), dinv read; res, d1, z written (z read)
-  count_bytes(c, op_bytes(S, sizeof(TM)) + double(S.ncols) * (W * sizeof(T) + (scaled ? 0 : sizeof(T))) +
-                     double(S.nrows) * (sizeof(T) + W * sizeof(T) * (3 + (accumulate ? 1 : 0))));
-}
-}  // namespace
-
-template <class T>
-void cheb_first(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* r, const T* dinv, T theta_inv, T* d1,
-                T* res, T* z, T c1, T c2, int accumulate) {
-  // the velocity operator has a column-scaled copy S D^{-1}
-  const T* scaled = (&S == &c->sA && vals == avals<T>(c).template as<T>()) ? pick<T>(c->AD64, c->AD32) : nullptr;
-  cheb_first_impl<T, T>(c, S, vals, (T)1, scaled, W, r, dinv, theta_inv, d1, res, z, c1, c2, accumulate);
-}
-
-void cheb_first_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* r,
-                   const float* dinv, float theta_inv, float* d1, float* res, float* z, float c1, float c2,
-                   int accumulate) {
-  cheb_first_impl<float, _Float16>(c, S, vals, ms, nullptr, W, r, dinv, theta_inv, d1, res, z, c1, c2, accumulate);
-}
-
-void cheb_first_h(stokes_ctx* c, int W, const float* r, const float* dinv, float theta_inv, float* q1, float* res,
-                  float* z, float c1, float c2) {
-  const Sell& S = c->sA;
-  const int G = lanes_op(c, &S, W, true);
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      hipLaunchKernelGGL((k_cheb_first_q<float, _Float16, WW, 0, GG, 8>), dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0,
-                         c->stream, S.nrows, S.idx(WW),
-                         (const _Float16*)c->AD16.as<_Float16>(), r, dinv, theta_inv, q1, res, z, c1, c2);
-    });
-  });
-  check_launch();
-  // half values, r gathered, dinv read; q1, res, z written
-  count_bytes(c, op_bytes(S, 2) + double(S.nrows) * 4.0 * (4.0 * W + 1.0));
-}
-
-void cheb_first_hb(stokes_ctx* c, int W, const float* r, const float* dinv, float theta_inv, uint16_t* q1,
-                   float* res, float* z, float c1, float c2, bool zw) {
-  const Sell& S = c->sA;
-  const int G = lanes_qb(c, W);
-  int wp = W;
-  bool il = false;
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    wp = bf_width<WW>();
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      if (c->vel_il && c->AD16i.p) {  // the eight-slot interleaved copies
-        auto kern = zw ? k_cheb_first_qb<_Float16, WW, 0, GG, 8, true> : k_cheb_first_qb<_Float16, WW, 2, GG, 8, true>;
-        hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0, c->stream, S.nrows,
-                           vel_il_idx(c, WW, il_width<_Float16>()),
-                           (const _Float16*)c->AD16i.as<_Float16>(), r, dinv, theta_inv, q1, res, z, c1, c2);
-        il = true;
-        return;
-      }
-      auto kern = zw ? k_cheb_first_qb<_Float16, WW, 0, GG> : k_cheb_first_qb<_Float16, WW, 2, GG>;
-      hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW),
-                         (const _Float16*)c->AD16.as<_Float16>(), r, dinv, theta_inv, q1, res, z, c1, c2);
-    });
-  });
-  check_launch();
-  // half values, r gathered; res (floats) and q1 (bfloat16) written; dinv
-  // read and z written unless deferred
-  count_bytes(c, op_bytes(S, 2, !il || c->vel_af) +
-                     double(S.nrows) * (4.0 * (2.0 * W) + 2.0 * wp + (zw ? 4.0 * (W + 1.0) : 0.0)));
-}
-
-void cheb_step_hb(stokes_ctx* c, int W, const uint16_t* q, uint16_t* qn, const float* res_in, float* res_out,
-                  float* z, const float* dinv, float c1, float c2, const QSum* fin, bool zw) {
-  const Sell& S = c->sA;
-  // the timed launches: the steps that carry the iterate (deferred or not), not the closing one
-  const bool timed = fin == nullptr && prof_begin(c, &S, nullptr, nullptr);
-  const int zm = fin ? 2 : zw ? 0 : 1;
-  QSum fa{};
-  if (fin) {
-    if (fin->n < 0 || fin->n > kQSumMax) throw Error(STOKES_ERR_ARG, "deferred Chebyshev sum too long");
-    fa = *fin;
-  }
-  const int G = lanes_qb(c, W);
-  int wp = W;
-  bool il = false;
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    wp = bf_width<WW>();
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      const int nb = grid_full(S.nrows * GG);
-      if constexpr (BfRaw<bf_width<WW>(), WW / GG>::kOn) {
-        if (c->vel_il && c->AD16i.p) {  // the eight-slot interleaved copies
-          auto kern = zm == 0   ? k_cheb_step_qb<_Float16, WW, GG, 8, true, 0>
-                      : zm == 1 ? k_cheb_step_qb<_Float16, WW, GG, 8, true, 1>
-                                : k_cheb_step_qb<_Float16, WW, GG, 8, true, 2>;
-          hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, vel_il_idx(c, WW, il_width<_Float16>()),
-                             (const _Float16*)c->AD16i.as<_Float16>(), q, qn, res_in, res_out, z, dinv, c1, c2, fa);
-          il = true;
-          return;
-        }
-      }
-      auto kern = zm == 0   ? k_cheb_step_qb<_Float16, WW, GG, 8, false, 0>
-                  : zm == 1 ? k_cheb_step_qb<_Float16, WW, GG, 8, false, 1>
-                            : k_cheb_step_qb<_Float16, WW, GG, 8, false, 2>;
-      hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW),
-                         (const _Float16*)c->AD16.as<_Float16>(), q, qn, res_in, res_out, z, dinv, c1, c2, fa);
-    });
-  });
-  check_launch();
-  // algorithmic bytes: the stored operator once (half values of every padded
-  // entry, the column-index structure it reads: slot words alone for the
-  // affine slices of the interleaved copy); q read once (gathered and own
-  // row, WP bfloat16); res_in read (W floats); then
-  //   carrying z:  res_out and z written, z and dinv read, qn written;
-  //   deferred:    res_out and qn written;
-  //   closing:     r and the n earlier directions read, dinv read, z written
-  const double vec = zm == 0   ? 4.0 * (W * 4.0 + 1.0) + 2.0 * 2.0 * wp
-                     : zm == 1 ? 4.0 * (W * 2.0) + 2.0 * 2.0 * wp
-                               : 4.0 * (W * 3.0 + 1.0) + 2.0 * wp * (1.0 + fa.n);
-  const double bytes = op_bytes(S, 2, !il || c->vel_af) + double(S.nrows) * vec;
-  count_bytes(c, bytes);
-  if (timed) prof_end(c, bytes);
-}
-
-void cheb_step_h(stokes_ctx* c, int W, const float* q, float* qn, const float* res_in, float* res_out, float* z,
-                 const float* dinv, float c1, float c2) {
-  const Sell& S = c->sA;
-  const bool timed = prof_begin(c, &S, nullptr, nullptr);
-  const int G = lanes_op(c, &S, W, true);
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW),
-                           (const _Float16*)c->AD16.as<_Float16>(), q, qn, res_in, res_out, z, dinv, c1, c2);
-      };
-      go(k_cheb_step_q<float, _Float16, WW, GG, 8>);
-    });
-  });
-  check_launch();
-  // algorithmic bytes: the stored operator once (half values of every padded
-  // entry, the column-index structure); q gathered once; res_in, q, z read;
-  // res_out, qn, z written (W floats each); dinv read
-  const double bytes = op_bytes(S, 2) + double(S.nrows) * 4.0 * (W * 6.0 + 1.0);
-  count_bytes(c, bytes);
-  if (timed) prof_end(c, bytes);
-}
-
-void cheb_step_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* d, float* dn,
-                  const float* res_in, float* res_out, float* z, const float* dinv, float c1, float c2) {
-  const int G = lanes_op(c, &S, W, true);
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    if (S.es > 1 && with_e<WW>(S.es, [&](auto Ec) {
-          constexpr int EE = decltype(Ec)::value;
-          hipLaunchKernelGGL((k_cheb_step_es<float, WW, EE, _Float16>), dim3(grid_full(S.nrows * EE)), dim3(kBlock),
-                             0, c->stream, S.nrows, S.idx(WW), vals, ms, d, dn, res_in, res_out, z, dinv, c1, c2);
-        }))
-      return;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      hipLaunchKernelGGL((k_cheb_step<float, WW, 0, GG, _Float16>), dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0,
-                         c->stream, S.nrows, S.idx(WW), vals, ms, d, dn, res_in, res_out, z, dinv, c1, c2,
-                         (const float*)nullptr, (Scalars*)nullptr, 1, 0, 0, partials(c));
-    });
-  });
-  check_launch();
-  // half values, d gathered; res_in, z, dinv read; res_out, dn, z written
-  count_bytes(c, op_bytes(S, 2) + double(S.ncols) * W * 4.0 + double(S.nrows) * 4.0 * (W * 5.0 + 1.0));
-}
-
-template <class T>
-void cheb_step(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* d, T* dn, const T* res_in, T* res_out,
-               T* z, const T* dinv, T c1, T c2, const T* rvec, Scalars* sc, int cps, int nsys, int first) {
-  // the timed kernel is the plain Chebyshev step (no fused dot) on the velocity block
-  const bool timed = rvec == nullptr && prof_begin(c, &S, (const void*)vals, (const void*)avals<T>(c).template as<T>());
-  const int G = lanes_op(c, &S, W, std::is_same<T, float>::value);
-  dispatch_w(W, [&](auto Wc) {
-    constexpr int WW = decltype(Wc)::value;
-    if (!rvec && S.es > 1 && with_e<WW>(S.es, [&](auto Ec) {
-          constexpr int EE = decltype(Ec)::value;
-          hipLaunchKernelGGL((k_cheb_step_es<T, WW, EE>), dim3(grid_full(S.nrows * EE)), dim3(kBlock), 0, c->stream,
-                             S.nrows, S.idx(WW), vals, (T)1, d, dn, res_in, res_out, z, dinv, c1, c2);
-        }))
-      return;
-    with_g<WW>(G, [&](auto Gc) {
-      constexpr int GG = decltype(Gc)::value;
-      const int nb = grid_for(S.nrows * GG);
-      if (rvec) {
-        hipLaunchKernelGGL((k_cheb_step<T, WW, 1, GG>), dim3(nb), dim3(kBlock), 0, c->stream, S.nrows,
-                           S.idx(WW), vals, (T)1, d, dn, res_in, res_out, z, dinv, c1,
-                           c2, rvec, sc, cps, nsys, first, partials(c));
-        finish<WW>(c, S.nrows * GG, FIN_RHO, WW, sc, cps, nsys, first, nullptr);
-      } else
-        hipLaunchKernelGGL((k_cheb_step<T, WW, 0, GG>), dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0, c->stream, S.nrows,
-                           S.idx(WW), vals, (T)1, d, dn, res_in, res_out, z, dinv, c1,
-                           c2, rvec, sc, cps, nsys, first, partials(c));
-    });
-  });
-  check_launch();
-  // algorithmic bytes: the stored operator once (values of every padded
-  // entry, the column-index structure); d gathered once; res_in, z, dinv
-  // (and rvec) read; res_out, dn, z written
-  const double bytes = op_bytes(S, sizeof(T)) + double(S.ncols) * W * sizeof(T) +
-                       double(S.nrows) * sizeof(T) * (W * (rvec ? 6.0 : 5.0) + 1.0);
-  count_bytes(c, bytes);
-  if (timed) prof_end(c, bytes);
 }
 
 // Tuning cache (STOKES_TUNE_CACHE = path of a text file): one line
@@ -1018,7 +555,7 @@ void adj_jp(stokes_ctx* c, int nrb, double* g) {
 void adj_dJdf(stokes_ctx* c, int nrb, const double* lam, double* out) {
   dispatch_dn(c->dim, nrb, [&](auto Dc, auto Nc) {
     constexpr int D = decltype(Dc)::value, N = decltype(Nc)::value;
-    hipLaunchKernelGGL((k_adj_dJdf<D, N>), dim3(grid_for(c->n_p2)), dim3(kBlock), 0, c->stream, c->n_p2,
+    hipLaunchKernelGGL((k_adj_dJdf<D, N>), dim3(grid_full(c->n_p2 * kCsrLanes)), dim3(kBlock), 0, c->stream, c->n_p2,
                        c->nat2int.as<int32_t>(), c->p2full.rowptr.as<int32_t>(), c->p2full.cols.as<int32_t>(),
                        c->M_full.as<double>(), lam, out);
   });
@@ -1030,11 +567,11 @@ void adj_dJdf(stokes_ctx* c, int nrb, const double* lam, double* out) {
 void adj_dJdmu(stokes_ctx* c, int nrb, const double* u_full, const double* lam, double* res_dev) {
   dispatch_dn(c->dim, nrb, [&](auto Dc, auto Nc) {
     constexpr int D = decltype(Dc)::value, N = decltype(Nc)::value;
-    hipLaunchKernelGGL((k_adj_dJdmu<D, N>), dim3(grid_for(c->n_int)), dim3(kBlock), 0, c->stream, c->n_int, c->n_p2,
+    hipLaunchKernelGGL((k_adj_dJdmu<D, N>), dim3(grid_for(c->n_int * kCsrLanes)), dim3(kBlock), 0, c->stream, c->n_int, c->n_p2,
                        c->int2nat.as<int32_t>(), c->p2full.rowptr.as<int32_t>(), c->p2full.cols.as<int32_t>(),
                        c->L_full.as<double>(), c->strain ? c->D_full.as<double>() : nullptr, u_full, lam, res_dev,
                        partials(c));
-    finish<N>(c, c->n_int, FIN_STORE, N, nullptr, 1, 0, 0, res_dev);
+    finish<N>(c, c->n_int * kCsrLanes, FIN_STORE, N, nullptr, 1, 0, 0, res_dev);
   });
   check_launch();
   const double W = double(c->dim) * nrb;
@@ -1044,7 +581,6 @@ void adj_dJdmu(stokes_ctx* c, int nrb, const double* u_full, const double* lam, 
 
 #define INST(T)                                                                                                      \
   template void spmv<T>(stokes_ctx*, const Sell&, const T*, int, const T*, T*, T, const T*, T);                     \
-  template void Bmul<T>(stokes_ctx*, int, const T*, T*, T, const T*, T);                                            \
   template void Btmul<T>(stokes_ctx*, int, const T*, const T*, T*, T, const T*, T, T*);                             \
   template void momentum<T>(stokes_ctx*, int, const T*, const T*, const T*, T*, T, const T*);                       \
   template void velop<T>(stokes_ctx*, int, const T*, T*, T, const T*, T);                                           \
@@ -1055,14 +591,6 @@ void adj_dJdmu(stokes_ctx* c, int nrb, const double* u_full, const double* lam, 
   template void normalize_pressure<T>(stokes_ctx*, int, T*);                                                        \
   template void axpby<T>(stokes_ctx*, int64_t, T, const T*, T, T*);                                                 \
   template void axpy_sys<T>(stokes_ctx*, int64_t, int, int, const double*, double, const T*, T*);                   \
-  template void cg_spmv<T>(stokes_ctx*, int64_t, const Sell*, const T*, int, const T*, const T*, T*, T*, Scalars*, int, \
-                           int);                                                                                 \
-  template void cg_update<T>(stokes_ctx*, int64_t, int, int, T*, T*, const T*, const T*, const T*, T, T*, T*,       \
-                             Scalars*, int, int);                                                                    \
-  template void cheb_init<T>(stokes_ctx*, int64_t, int, const T*, const T*, T, T*, T*);                             \
-  template void cheb_first<T>(stokes_ctx*, const Sell&, const T*, int, const T*, const T*, T, T*, T*, T*, T, T, int); \
-  template void cheb_step<T>(stokes_ctx*, const Sell&, const T*, int, const T*, T*, const T*, T*, T*, const T*, T,  \
-                             T, const T*, Scalars*, int, int, int);                                                  \
   template void vel_in<T>(stokes_ctx*, int, const double*, T*);                                                     \
   template void vel_out<T>(stokes_ctx*, int, const T*, const double*, double*, int);                                \
   template void p_in<T>(stokes_ctx*, int, const double*, T*);                                                       \
