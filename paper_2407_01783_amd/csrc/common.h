@@ -146,6 +146,12 @@ struct VmgLevel {
   DevBuf pv64, pv32, rv64, rv32;
 };
 
+// Dense inverse of a coarsest multigrid operator: rows of ld values (pads 0).
+struct DenseInv {
+  int64_t n = 0, ld = 0;  // n = 0: none
+  DevBuf i64, i32;
+};
+
 // A multigrid hierarchy on the nested Kuhn meshes n, n/2, ...  Level views
 // point either at context-owned operators or at levels in `own`.
 struct MgHier {
@@ -160,8 +166,7 @@ struct MgHier {
   };
   std::vector<View> lv;
   std::vector<std::unique_ptr<MgLevel>> own;
-  int64_t dense_n = 0;        // > 0: the coarsest level is solved by a dense inverse
-  DevBuf cinv64, cinv32;      // [n][n] inverse of the coarsest operator
+  DenseInv dense;  // of the coarsest level (n = 0: a polynomial over its whole spectrum)
 };
 
 // GPU time of one solver phase, from pairs of HIP events recorded on the
@@ -256,7 +261,14 @@ struct stokes_ctx {
   stokes::DevBuf rperm;                 // that schedule over the interior (velocity) rows
   int zblock = -1;                       // lattice planes per block of the interior row order (0: whole slab, -1: by size)
   int mg_es = 1;                        // pressure-MG lanes per row: 1 by level size, -1 timed, 0 one lane, 2-16 fixed
-  int64_t mg_dense_max = 1500;          // largest level solved densely
+  // Largest multigrid level solved by its dense inverse.  The product streams
+  // the inverse (FP32 / FP64: 4,913 rows 17 / 29 us, 8,000 rows 38 / 93 us,
+  // 10,648 rows 85 / 165 us).  mg_dense_max, where the level could coarsen
+  // further: smoothing, residuals and transfers of a level of some thousand
+  // rows and the solve below it are ten launches of 4-5 us, 36 / 40 us.
+  // mg_dense_last, where it cannot (an odd cell count): the polynomial over
+  // the whole spectrum is 24 launches, 100-140 / 150 us, and less exact.
+  int64_t mg_dense_max = 5000, mg_dense_last = 9000;
   double mg_smooth_ratio = 10.0;
   int use_mgx = 1;                      // lumped CC: precondition with mgx (0: mgq)
   // P3/P2: build the Galerkin hierarchy too (0: only the eps M_Q + L_Q one),
@@ -271,8 +283,7 @@ struct stokes_ctx {
   std::vector<std::unique_ptr<stokes::VmgLevel>> vmg;
   bool vmg_built = false;
   double vmg_mu = -1.0;                 // mu the hierarchy was built for
-  int64_t vmg_dense_n = 0;              // rows of the coarsest level if solved densely
-  stokes::DevBuf vmg_cinv64, vmg_cinv32;
+  stokes::DenseInv vmg_dense;           // of the coarsest level
   int vmg_smooth_degree = 3;
 
   // lanes per row of the velocity-row kernels, key W * 2 + (FP32 ? 1 : 0)

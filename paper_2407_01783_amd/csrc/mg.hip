@@ -15,8 +15,9 @@
 //   * smoothing: Chebyshev-Jacobi on the upper part of each level's spectrum,
 //     the same polynomial before and after the coarse correction, so the
 //     cycle is symmetric and can precondition CG;
-//   * coarsest level: an exact dense inverse when it has at most 1500
-//     vertices, else a Chebyshev polynomial over its whole spectrum.
+//   * coarsest level: an exact dense inverse where that is cheaper than what
+//     it replaces (build_mg), else a Chebyshev polynomial over its whole
+//     spectrum.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -114,60 +115,6 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(int nf, int nc, const T*
   }
 }
 
-// y[i][r] = sum_j Cinv[i][j] x[j][r]   (coarsest-level solve): one wavefront
-// per row, coalesced over j, wavefront-shuffle reduction
-template <typename T, int NRB>
-__global__ __launch_bounds__(kBlock) void k_dense_mv(int64_t n, const T* __restrict__ Ci, const T* __restrict__ x,
-                                                     T* __restrict__ y) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (row >= n) return;  // whole wavefronts exit together
-  double acc[NRB];
-#pragma unroll
-  for (int r = 0; r < NRB; ++r) acc[r] = 0;
-  for (int64_t j = lane; j < n; j += 64) {
-    const double a = Ci[row * n + j];
-#pragma unroll
-    for (int r = 0; r < NRB; ++r) acc[r] += a * (double)x[j * NRB + r];
-  }
-#pragma unroll
-  for (int r = 0; r < NRB; ++r) acc[r] = wave_sum(acc[r]);
-  if (lane == 0)
-#pragma unroll
-    for (int r = 0; r < NRB; ++r) y[row * NRB + r] = (T)acc[r];
-}
-
-// Inverse of a small SPD matrix by Cholesky (host).
-std::vector<double> spd_inverse(std::vector<double> A, int64_t n) {
-  for (int64_t j = 0; j < n; ++j) {  // A = L L^T in place (lower)
-    double d = A[j * n + j];
-    for (int64_t k = 0; k < j; ++k) d -= A[j * n + k] * A[j * n + k];
-    if (!(d > 0)) throw Error(STOKES_ERR_BREAKDOWN, "coarsest multigrid operator is not positive definite");
-    d = std::sqrt(d);
-    A[j * n + j] = d;
-    for (int64_t i = j + 1; i < n; ++i) {
-      double s = A[i * n + j];
-      for (int64_t k = 0; k < j; ++k) s -= A[i * n + k] * A[j * n + k];
-      A[i * n + j] = s / d;
-    }
-  }
-  std::vector<double> inv(n * n, 0.0), col(n);
-  for (int64_t c = 0; c < n; ++c) {  // solve L L^T x = e_c
-    for (int64_t i = 0; i < n; ++i) {
-      double s = i == c ? 1.0 : 0.0;
-      for (int64_t k = 0; k < i; ++k) s -= A[i * n + k] * col[k];
-      col[i] = s / A[i * n + i];
-    }
-    for (int64_t i = n - 1; i >= 0; --i) {
-      double s = col[i];
-      for (int64_t k = i + 1; k < n; ++k) s -= A[k * n + i] * col[k];
-      col[i] = s / A[i * n + i];
-    }
-    for (int64_t i = 0; i < n; ++i) inv[i * n + c] = col[i];
-  }
-  return inv;
-}
-
 struct Cheb {
   double theta_inv;
   std::vector<double> c1, c2;
@@ -227,28 +174,6 @@ __global__ __launch_bounds__(kBlock) void k_csr_w(int64_t nrows, const int32_t* 
   }
 }
 
-// y[i][w] = sum_j Cinv[i][j] x[j][w]: one wavefront per row
-template <typename T, int W>
-__global__ __launch_bounds__(kBlock) void k_dense_mv_w(int64_t n, const T* __restrict__ Ci, const T* __restrict__ x,
-                                                       T* __restrict__ y) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (row >= n) return;  // whole wavefronts exit together
-  double acc[W];
-#pragma unroll
-  for (int w = 0; w < W; ++w) acc[w] = 0;
-  for (int64_t j = lane; j < n; j += 64) {
-    const double a = Ci[row * n + j];
-#pragma unroll
-    for (int w = 0; w < W; ++w) acc[w] += a * (double)x[j * W + w];
-  }
-#pragma unroll
-  for (int w = 0; w < W; ++w) acc[w] = wave_sum(acc[w]);
-  if (lane == 0)
-#pragma unroll
-    for (int w = 0; w < W; ++w) y[row * W + w] = (T)acc[w];
-}
-
 template <class F>
 void dispatch_w_mg(int W, F&& f) {
   switch (W) {
@@ -264,45 +189,13 @@ void dispatch_w_mg(int W, F&& f) {
   }
 }
 
-// dense symmetric matrix of a scalar sliced-ELL operator (host)
-std::vector<double> sell_dense(stokes_ctx* c, const Sell& S, const DevBuf& v64) {
-  const int64_t nr = S.nrows;
-  std::vector<int64_t> sp(S.nslices + 1);
-  std::vector<int32_t> cols(S.nnz_pad);
-  std::vector<double> vals(S.nnz_pad);
-  HIP_CHECK(hipStreamSynchronize(c->stream));
-  HIP_CHECK(hipMemcpy(sp.data(), S.slice_ptr.p, sp.size() * sizeof(int64_t), hipMemcpyDeviceToHost));
-  HIP_CHECK(hipMemcpy(cols.data(), S.cols.p, cols.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-  HIP_CHECK(hipMemcpy(vals.data(), v64.p, vals.size() * sizeof(double), hipMemcpyDeviceToHost));
-  std::vector<double> A(nr * nr, 0.0);
-  for (int64_t r = 0; r < nr; ++r)
-    for (int64_t k = sp[r / 64] + r % 64; k < sp[r / 64 + 1]; k += 64) A[r * nr + cols[k]] += vals[k];
-  return A;
-}
 }  // namespace
 
 // Dense inverse of the coarsest level when it is small enough.
 static void dense_coarsest(stokes_ctx* c, MgHier& H) {
   const MgHier::View& V = H.lv.back();
-  const Sell& S = *V.S;
-  const int64_t nr = S.nrows;
-  H.dense_n = 0;
-  if (nr > c->mg_dense_max) return;
-  std::vector<int64_t> sp(S.nslices + 1);
-  std::vector<int32_t> cols(S.nnz_pad);
-  std::vector<double> vals(S.nnz_pad);
-  HIP_CHECK(hipStreamSynchronize(c->stream));
-  HIP_CHECK(hipMemcpy(sp.data(), S.slice_ptr.p, sp.size() * sizeof(int64_t), hipMemcpyDeviceToHost));
-  HIP_CHECK(hipMemcpy(cols.data(), S.cols.p, cols.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-  HIP_CHECK(hipMemcpy(vals.data(), V.v64->p, vals.size() * sizeof(double), hipMemcpyDeviceToHost));
-  std::vector<double> A(nr * nr, 0.0);
-  for (int64_t r = 0; r < nr; ++r)
-    for (int64_t k = sp[r / 64] + r % 64; k < sp[r / 64 + 1]; k += 64) A[r * nr + cols[k]] += vals[k];
-  const std::vector<double> inv = spd_inverse(A, nr);
-  std::vector<float> inv32(inv.begin(), inv.end());
-  upload(H.cinv64, inv);
-  upload(H.cinv32, inv32);
-  H.dense_n = nr;
+  H.dense.n = 0;
+  if (V.S->nrows <= c->mg_dense_last) dense_inverse(c, *V.S, V.v64->as<const double>(), H.dense);
 }
 
 // Entry-split lanes per level (Sell::es).  The coarse levels have a few
@@ -415,7 +308,7 @@ void build_mg(stokes_ctx* c) {
   // stays symmetric positive definite and is the better preconditioner.
   c->mgx.lv.clear();
   c->mgx.own.clear();
-  c->mgx.dense_n = 0;
+  c->mgx.dense.n = 0;
   if (fm.order != 3 || c->mgx_p3) {
     assemble_galerkin(c, c->mgx);
     dense_coarsest(c, c->mgx);
@@ -480,16 +373,8 @@ void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int lv
     }
   };
   if (lv == nlev - 1) {  // coarsest: dense inverse, or a polynomial over the whole spectrum
-    if (H.dense_n == nr) {
-      const T* Ci = ops::pick<T>(H.cinv64, H.cinv32);
-      dispatch_dn(c->dim, nrb, [&](auto Dc, auto Nc) {
-        constexpr int N = decltype(Nc)::value;
-        (void)Dc;
-        hipLaunchKernelGGL((k_dense_mv<T, N>), dim3((nr + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
-                           c->stream, nr, Ci, r, e);
-      });
-      ops::check_launch();
-      ops::count_bytes(c, double(nr) * nr * sizeof(T) + 2.0 * nr * nrb * sizeof(T));  // dense inverse, r, e
+    if (H.dense.n == nr) {
+      dense_solve<T>(c, H.dense, nrb, r, e);
     } else {
       cheb(bf, c->mg_coarse_degree, r, e, 0);
     }
@@ -549,7 +434,7 @@ template void mg_vcycle<float>(stokes_ctx*, const MgHier&, int, const float*, fl
 
 void build_vmg(stokes_ctx* c) {
   c->vmg.clear();
-  c->vmg_dense_n = 0;
+  c->vmg_dense.n = 0;
   const HostMesh& fm = c->mesh;
   const int D = fm.dim;
   int nf = fm.n, stride = 1;
@@ -604,22 +489,9 @@ void build_vmg(stokes_ctx* c) {
     nf = nc;
   }
   // coarsest level: dense inverse when small
-  if (!c->vmg.empty()) {
-    VmgLevel& L = *c->vmg.back();
-    if (L.nrows <= c->mg_dense_max) {
-      const std::vector<double> inv = spd_inverse(sell_dense(c, L.S, L.v64), L.nrows);
-      std::vector<float> inv32(inv.begin(), inv.end());
-      upload(c->vmg_cinv64, inv);
-      upload(c->vmg_cinv32, inv32);
-      c->vmg_dense_n = L.nrows;
-    }
-  } else if (c->n_int <= c->mg_dense_max) {
-    const std::vector<double> inv = spd_inverse(sell_dense(c, c->sA, c->A64), c->n_int);
-    std::vector<float> inv32(inv.begin(), inv.end());
-    upload(c->vmg_cinv64, inv);
-    upload(c->vmg_cinv32, inv32);
-    c->vmg_dense_n = c->n_int;
-  }
+  const Sell& Sc = c->vmg.empty() ? c->sA : c->vmg.back()->S;
+  const DevBuf& vc = c->vmg.empty() ? c->A64 : c->vmg.back()->v64;
+  if (Sc.nrows <= c->mg_dense_last) dense_inverse(c, Sc, vc.as<const double>(), c->vmg_dense);
   HIP_CHECK(hipStreamSynchronize(c->stream));
   c->vmg_mu = c->prob.mu;
   c->vmg_built = true;
@@ -652,15 +524,8 @@ void vel_vcycle(stokes_ctx* c, int W, const T* r, T* e, int lv) {
     }
   };
   if (lv == nlev - 1) {  // coarsest
-    if (c->vmg_dense_n == nr) {
-      const T* Ci = ops::pick<T>(c->vmg_cinv64, c->vmg_cinv32);
-      dispatch_w_mg(W, [&](auto Wc) {
-        constexpr int WW = decltype(Wc)::value;
-        hipLaunchKernelGGL((k_dense_mv_w<T, WW>), dim3((nr + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
-                           c->stream, nr, Ci, r, e);
-      });
-      ops::check_launch();
-      ops::count_bytes(c, double(nr) * nr * sizeof(T) + 2.0 * nr * W * sizeof(T));
+    if (c->vmg_dense.n == nr) {
+      dense_solve<T>(c, c->vmg_dense, W, r, e);
     } else {
       cheb(bf, c->mg_coarse_degree, r, e, 0);
     }

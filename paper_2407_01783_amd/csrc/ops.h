@@ -20,6 +20,11 @@ void assemble_galerkin(stokes_ctx* c, MgHier& H);
 // e = one multigrid V-cycle of hierarchy H applied to r (pressure layout)
 template <class T>
 void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int level = 0);
+// dense inverse of a coarsest level (formed on the device) and y = D x for W
+// interleaved values per row (dense.hip)
+void dense_inverse(stokes_ctx* c, const Sell& S, const double* v64, DenseInv& D);
+template <class T>
+void dense_solve(stokes_ctx* c, const DenseInv& D, int W, const T* x, T* y);
 // velocity multigrid: coarse level assembly, hierarchy build, one V-cycle of
 // alpha M + mu L applied to W = dim x nrhs interleaved components
 void assemble_p2_level(stokes_ctx* c, const HostMesh& m, VmgLevel& L);
