@@ -539,9 +539,13 @@ stokes_status stokes_assemble(const stokes_problem* prob, void* hip_stream, stok
     c->prob = *prob;
     c->strain = (prob->flags & STOKES_FLAG_STRAIN) != 0;
     HIP_CHECK(hipGetDevice(&c->device));
+    int lds = 0;
+    HIP_CHECK(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
+    c->lds_bytes = size_t(lds);
     (void)scratch_on(c->device);  // set-up of the allocation-free residual, once per device
     c->user_stream = static_cast<hipStream_t>(hip_stream);
     if (const char* e = std::getenv("STOKES_GRAPHS")) c->use_graphs = std::atoi(e) != 0;
+    if (const char* e = std::getenv("STOKES_PCG_SMALL")) c->pcg_small = std::atoi(e) != 0;
     if (const char* e = std::getenv("STOKES_CG_CHECK")) c->cg_check_every = std::max(1, std::atoi(e));
     if (const char* e = std::getenv("STOKES_MGX")) c->use_mgx = std::atoi(e) != 0;
     if (const char* e = std::getenv("STOKES_MGX_P3")) c->mgx_p3 = std::atoi(e) != 0;

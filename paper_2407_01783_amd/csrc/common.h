@@ -184,6 +184,7 @@ struct Scalars {
   double sigma[kMaxSys], rr[kMaxSys], bb[kMaxSys], tol2[kMaxSys];
   int active[kMaxSys];
   int breakdown;
+  int iters;  // of a single-launch CG
 };
 
 }  // namespace stokes
@@ -319,6 +320,8 @@ struct stokes_ctx {
   };
   std::map<std::string, Graph> graphs;
   int use_graphs = 1;
+  int pcg_small = 1;       // small velocity systems: the whole inner CG in one launch
+  size_t lds_bytes = 0;    // LDS a workgroup may use
   int cg_check_every = 2;  // inner CG: iterations between host convergence checks
 
   void* workspace(const std::string& name, size_t bytes) {

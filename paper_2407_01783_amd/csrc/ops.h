@@ -159,6 +159,15 @@ void cheb_first_h(stokes_ctx* c, int W, const float* r, const float* dinv, float
 void cheb_step_h(stokes_ctx* c, int W, const float* q, float* qn, const float* res_in, float* res_out, float* z,
                  const float* dinv, float c1, float c2);
 
+// The inner velocity CG (Chebyshev-Jacobi preconditioner, no augmented
+// Lagrangian) of a small system in one launch (pcg_small.hip): fits says
+// whether the system does; the outcome goes to *sc.
+template <class T>
+bool pcg_small_fits(stokes_ctx* c, int W, int degree);
+template <class T>
+void pcg_small(stokes_ctx* c, int W, int cps, int degree, T thinv, const double* c1, const double* c2, double rtol,
+               int maxit, const T* b, T* x, T* r, T* p, T* q, T* res, T* z, Scalars* sc);
+
 // layout transfers
 template <class T>
 void vel_in(stokes_ctx* c, int nrb, const double* src, T* dst);

@@ -199,6 +199,7 @@ class Engine {
     const Sell* S = nullptr;  // fused scalar SELL operator, or
     std::function<void(const T*, T*)> apply;  // composite t = X z
     std::function<void(const T*, T*)> extra;  // added term (augmented Lagrangian)
+    bool small = false;  // the velocity operator alone: may run in one launch
   };
   struct Prec {
     const Sell* S;
@@ -225,6 +226,23 @@ class Engine {
     T* d0 = buf(tag + "_d0", n);
     T* d1 = buf(tag + "_d1", n);
     T* res = buf(tag + "_res", n);
+    if (op.small && !pc.apply && ops::pcg_small_fits<T>(c_, W, pc.degree)) {
+      const ChebCoef k = cheb_coef(pc.b, pc.degree);
+      ops::pcg_small<T>(c_, W, cps, pc.degree, pc.degree > 1 ? (T)k.theta_inv : (T)1, k.c1.data(), k.c2.data(), rtol,
+                        fixed > 0 ? fixed : maxit, b, x, r, p, q, res, z, sc);
+      sync_scalars(sc_index);
+      const int run = c_->h_scal->iters;
+      check_breakdown(tag, run, nsys);
+      // counted as the launches below count: the operator and each step of the
+      // polynomial once per iteration, host checks every cg_check_every
+      const double vec = double(n) * sizeof(T);
+      ops::count_bytes(c_, (run + 1.0) * (pc.degree - 1) * (ops::op_bytes(c_->sA, sizeof(T)) + 6 * vec) +
+                               run * (ops::op_bytes(c_->sA, sizeof(T)) * (c_->strain ? 0.5 * D_ * (D_ + 1) : 1.0) +
+                                      13 * vec));
+      if (fixed > 0) return fixed;
+      const int every = std::max(1, c_->cg_check_every);
+      return std::min(maxit, (run + every - 1) / every * every);
+    }
     T* t = (op.apply || op.extra) ? buf(tag + "_t", n) : nullptr;
     ops::zero_dev(c_, x, n * sizeof(T));
     ops::zero_dev(c_, p, n * sizeof(T));
@@ -303,17 +321,7 @@ class Engine {
     for (;;) {
       sync_scalars(sc_index);
       const Scalars& h = *c_->h_scal;
-      if (h.breakdown) {
-        std::string msg = "inner CG '" + tag + "' breakdown (non-positive curvature) at iteration " +
-                          std::to_string(it) + ":";
-        for (int s2 = 0; s2 < nsys; ++s2) {
-          char b[160];
-          std::snprintf(b, sizeof(b), " [sys %d rho %.3e sigma %.3e rr %.3e bb %.3e active %d]", s2, h.rho[s2],
-                        h.sigma[s2], h.rr[s2], h.bb[s2], h.active[s2]);
-          msg += b;
-        }
-        throw Error(STOKES_ERR_BREAKDOWN, msg);
-      }
+      check_breakdown(tag, it, nsys);
       bool any = false;
       for (int s = 0; s < nsys; ++s) any = any || h.active[s];
       if (!any || it >= maxit) {
@@ -333,6 +341,20 @@ class Engine {
       it += k;
     }
     return it;
+  }
+
+  void check_breakdown(const std::string& tag, int it, int nsys) {
+    const Scalars& h = *c_->h_scal;
+    if (!h.breakdown) return;
+    std::string msg = "inner CG '" + tag + "' breakdown (non-positive curvature) at iteration " + std::to_string(it) +
+                      ":";
+    for (int s2 = 0; s2 < nsys; ++s2) {
+      char b[160];
+      std::snprintf(b, sizeof(b), " [sys %d rho %.3e sigma %.3e rr %.3e bb %.3e active %d]", s2, h.rho[s2],
+                    h.sigma[s2], h.rr[s2], h.bb[s2], h.active[s2]);
+      msg += b;
+    }
+    throw Error(STOKES_ERR_BREAKDOWN, msg);
   }
 
   void sync_scalars(int i) {
@@ -363,6 +385,7 @@ class Engine {
       return;
     }
     Op op;
+    op.small = gamma_ == 0;
     int cps = 1;
     if (c_->strain) {
       // alpha M + mu (L + D) couples the components; A~_{lambda,3} (the
