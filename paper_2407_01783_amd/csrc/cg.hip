@@ -12,10 +12,13 @@ void cg_spmv(stokes_ctx* c, int64_t nrows, const Sell* S, const T* vals, int W, 
     constexpr int WW = decltype(Wc)::value;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      hipLaunchKernelGGL((k_cg_spmv<T, WW, GG>), dim3(grid_for(nrows * GG)), dim3(kBlock), 0, c->stream, nrows,
-                         S ? S->idx(WW) : SellIdx{}, vals, z,
-                         extra, q, p, sc, cps, nsys, partials(c));
-      finish<WW>(c, nrows * GG, FIN_ALPHA, WW, sc, cps, nsys, 0, nullptr);
+      const int lg = S ? split_lg_dot(nrows, GG, WW / GG) : 0;
+      const int nb = lg ? grid_rows(nrows, GG, lg) : grid_for(nrows * GG);
+      with_split<GG, WW / GG>(lg, [&](auto SPc) {
+        hipLaunchKernelGGL((k_cg_spmv<T, WW, GG, decltype(SPc)::value>), dim3(nb), dim3(kBlock), 0, c->stream, nrows,
+                           S ? S->idx(WW) : SellIdx{}, vals, z, extra, q, p, sc, cps, nsys, partials(c), lg);
+      });
+      finish_n<WW>(c, nb, FIN_ALPHA, WW, sc, cps, nsys, 0, nullptr);
     });
   });
   check_launch();

@@ -20,18 +20,22 @@ void cheb_first_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, const T
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int nb = grid_full(S.nrows * GG);
-      auto go = [&](auto kern, const TM* v) {
-        hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), v, ms, r, dinv, theta_inv,
-                           d1, res, z, c1, c2);
-      };
-      if (scaled) {
-        if (accumulate) go(k_cheb_first<T, WW, 1, GG, 1, TM>, scaled);
-        else go(k_cheb_first<T, WW, 0, GG, 1, TM>, scaled);
-      } else {
-        if (accumulate) go(k_cheb_first<T, WW, 1, GG, 0, TM>, vals);
-        else go(k_cheb_first<T, WW, 0, GG, 0, TM>, vals);
-      }
+      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int nb = grid_rows(S.nrows, GG, lg);
+      with_split<GG, WW / GG>(lg, [&](auto SPc) {
+        constexpr bool SP = decltype(SPc)::value;
+        auto go = [&](auto kern, const TM* v) {
+          hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), v, ms, r, dinv, theta_inv,
+                             d1, res, z, c1, c2, lg);
+        };
+        if (scaled) {
+          if (accumulate) go(k_cheb_first<T, WW, 1, GG, 1, TM, SP>, scaled);
+          else go(k_cheb_first<T, WW, 0, GG, 1, TM, SP>, scaled);
+        } else {
+          if (accumulate) go(k_cheb_first<T, WW, 1, GG, 0, TM, SP>, vals);
+          else go(k_cheb_first<T, WW, 0, GG, 0, TM, SP>, vals);
+        }
+      });
     });
   });
   check_launch();
@@ -84,17 +88,20 @@ void cheb_first_hb(stokes_ctx* c, int W, const float* r, const float* dinv, floa
     wp = bf_width<WW>();
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      if (c->vel_il && c->AD16i.p) {  // the eight-slot interleaved copies
-        auto kern = zw ? k_cheb_first_qb<_Float16, WW, 0, GG, 8, true> : k_cheb_first_qb<_Float16, WW, 2, GG, 8, true>;
-        hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0, c->stream, S.nrows,
-                           vel_il_idx(c, WW, il_width<_Float16>()),
-                           (const _Float16*)c->AD16i.as<_Float16>(), r, dinv, theta_inv, q1, res, z, c1, c2);
-        il = true;
-        return;
-      }
-      auto kern = zw ? k_cheb_first_qb<_Float16, WW, 0, GG> : k_cheb_first_qb<_Float16, WW, 2, GG>;
-      hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW),
-                         (const _Float16*)c->AD16.as<_Float16>(), r, dinv, theta_inv, q1, res, z, c1, c2);
+      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int nb = grid_rows(S.nrows, GG, lg);
+      il = c->vel_il && c->AD16i.p;  // the eight-slot interleaved copies
+      with_split<GG, WW / GG>(lg, [&](auto SPc) {
+        constexpr bool SP = decltype(SPc)::value;
+        auto kern = il ? (zw ? k_cheb_first_qb<_Float16, WW, 0, GG, 8, true, SP>
+                             : k_cheb_first_qb<_Float16, WW, 2, GG, 8, true, SP>)
+                       : (zw ? k_cheb_first_qb<_Float16, WW, 0, GG, 8, false, SP>
+                             : k_cheb_first_qb<_Float16, WW, 2, GG, 8, false, SP>);
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows,
+                           il ? vel_il_idx(c, WW, il_width<_Float16>()) : S.idx(WW),
+                           (const _Float16*)(il ? c->AD16i : c->AD16).template as<_Float16>(), r, dinv, theta_inv, q1, res,
+                           z, c1, c2, lg);
+      });
     });
   });
   check_launch();

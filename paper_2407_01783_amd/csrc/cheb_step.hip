@@ -23,23 +23,28 @@ void cheb_step_hb(stokes_ctx* c, int W, const uint16_t* q, uint16_t* qn, const f
     wp = bf_width<WW>();
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int nb = grid_full(S.nrows * GG);
-      if constexpr (BfRaw<bf_width<WW>(), WW / GG>::kOn) {
-        if (c->vel_il && c->AD16i.p) {  // the eight-slot interleaved copies
-          auto kern = zm == 0   ? k_cheb_step_qb<_Float16, WW, GG, 8, true, 0>
-                      : zm == 1 ? k_cheb_step_qb<_Float16, WW, GG, 8, true, 1>
-                                : k_cheb_step_qb<_Float16, WW, GG, 8, true, 2>;
-          hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, vel_il_idx(c, WW, il_width<_Float16>()),
-                             (const _Float16*)c->AD16i.as<_Float16>(), q, qn, res_in, res_out, z, dinv, c1, c2, fa);
-          il = true;
-          return;
+      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int nb = grid_rows(S.nrows, GG, lg);
+      with_split<GG, WW / GG>(lg, [&](auto SPc) {
+        constexpr bool SP = decltype(SPc)::value;
+        if constexpr (BfRaw<bf_width<WW>(), WW / GG>::kOn) {
+          if (c->vel_il && c->AD16i.p) {  // the eight-slot interleaved copies
+            auto kern = zm == 0   ? k_cheb_step_qb<_Float16, WW, GG, 8, true, 0, SP>
+                        : zm == 1 ? k_cheb_step_qb<_Float16, WW, GG, 8, true, 1, SP>
+                                  : k_cheb_step_qb<_Float16, WW, GG, 8, true, 2, SP>;
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows,
+                               vel_il_idx(c, WW, il_width<_Float16>()), (const _Float16*)c->AD16i.as<_Float16>(), q, qn,
+                               res_in, res_out, z, dinv, c1, c2, fa, lg);
+            il = true;
+            return;
+          }
         }
-      }
-      auto kern = zm == 0   ? k_cheb_step_qb<_Float16, WW, GG, 8, false, 0>
-                  : zm == 1 ? k_cheb_step_qb<_Float16, WW, GG, 8, false, 1>
-                            : k_cheb_step_qb<_Float16, WW, GG, 8, false, 2>;
-      hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW),
-                         (const _Float16*)c->AD16.as<_Float16>(), q, qn, res_in, res_out, z, dinv, c1, c2, fa);
+        auto kern = zm == 0   ? k_cheb_step_qb<_Float16, WW, GG, 8, false, 0, SP>
+                    : zm == 1 ? k_cheb_step_qb<_Float16, WW, GG, 8, false, 1, SP>
+                              : k_cheb_step_qb<_Float16, WW, GG, 8, false, 2, SP>;
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW),
+                           (const _Float16*)c->AD16.as<_Float16>(), q, qn, res_in, res_out, z, dinv, c1, c2, fa, lg);
+      });
     });
   });
   check_launch();
@@ -96,9 +101,13 @@ void cheb_step_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, 
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      hipLaunchKernelGGL((k_cheb_step<float, WW, 0, GG, _Float16>), dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0,
-                         c->stream, S.nrows, S.idx(WW), vals, ms, d, dn, res_in, res_out, z, dinv, c1, c2,
-                         (const float*)nullptr, (Scalars*)nullptr, 1, 0, 0, partials(c));
+      const int lg = split_lg(S.nrows, GG, WW / GG);
+      with_split<GG, WW / GG>(lg, [&](auto SPc) {
+        hipLaunchKernelGGL((k_cheb_step<float, WW, 0, GG, _Float16, decltype(SPc)::value>),
+                           dim3(grid_rows(S.nrows, GG, lg)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), vals, ms, d,
+                           dn, res_in, res_out, z, dinv, c1, c2, (const float*)nullptr, (Scalars*)nullptr, 1, 0, 0,
+                           partials(c), lg);
+      });
     });
   });
   check_launch();
@@ -122,16 +131,15 @@ void cheb_step(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* d, T
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int nb = grid_for(S.nrows * GG);
-      if (rvec) {
-        hipLaunchKernelGGL((k_cheb_step<T, WW, 1, GG>), dim3(nb), dim3(kBlock), 0, c->stream, S.nrows,
-                           S.idx(WW), vals, (T)1, d, dn, res_in, res_out, z, dinv, c1,
-                           c2, rvec, sc, cps, nsys, first, partials(c));
-        finish<WW>(c, S.nrows * GG, FIN_RHO, WW, sc, cps, nsys, first, nullptr);
-      } else
-        hipLaunchKernelGGL((k_cheb_step<T, WW, 0, GG>), dim3(grid_full(S.nrows * GG)), dim3(kBlock), 0, c->stream, S.nrows,
-                           S.idx(WW), vals, (T)1, d, dn, res_in, res_out, z, dinv, c1,
-                           c2, rvec, sc, cps, nsys, first, partials(c));
+      const int lg = rvec ? split_lg_dot(S.nrows, GG, WW / GG) : split_lg(S.nrows, GG, WW / GG);
+      const int nb = rvec && !lg ? grid_for(S.nrows * GG) : grid_rows(S.nrows, GG, lg);
+      with_split<GG, WW / GG>(lg, [&](auto SPc) {
+        constexpr bool SP = decltype(SPc)::value;
+        auto kern = rvec ? k_cheb_step<T, WW, 1, GG, T, SP> : k_cheb_step<T, WW, 0, GG, T, SP>;
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), vals, (T)1, d, dn, res_in,
+                           res_out, z, dinv, c1, c2, rvec, sc, cps, nsys, first, partials(c), lg);
+      });
+      if (rvec) finish_n<WW>(c, nb, FIN_RHO, WW, sc, cps, nsys, first, nullptr);
     });
   });
   check_launch();

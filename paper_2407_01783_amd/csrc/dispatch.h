@@ -2,6 +2,7 @@
 // sides), lanes per row, and the operator values of a working precision.
 #pragma once
 
+#include <algorithm>
 #include <string>
 #include <type_traits>
 
@@ -49,6 +50,54 @@ void dispatch_dn(int D, int NRB, F&& f) {
 }
 
 inline double* partials(stokes_ctx* c) { return c->red.partials.as<double>(); }
+
+// Workgroups that cover `rows` rows in one pass of the XCD partition, G lanes
+// per row or 2^lg wavefronts per slice.
+inline int grid_rows(int64_t rows, int G, int lg) {
+  const int64_t xn = ((rows + 7) / 8 + 63) / 64 * 64, per = (kBlock / G) >> lg;
+  return static_cast<int>(8 * std::max<int64_t>(1, (xn + per - 1) / per));
+}
+
+// log2 of the wavefronts that share a slice in a product over `rows` rows with
+// G lanes per row and wg values per lane (rows_split in kernels.h).  Only the
+// widths 1 and 3: the others can be run by 2, 4 or 8 lanes per row, a choice
+// that is timed per context and must not change the sums.  The lines lie where
+// the card stops being short of wavefronts (2^14 fill it, at 64 rows each), by
+// the time of one product at lg = 0 / 1 / 2, in us:
+//   width 1   16 k rows: half product 6.1 / 4.9 / 4.0; 36 k: 6.0 / 6.1 / 5.2,
+//             first step 9.6 / 8.1 / 6.6; 69 k: 7.4 / 7.5 / 6.6, first step
+//             9.8 / 8.8 / 9.0; 119 k (200 entries a row): 49 / 48 / 43, first
+//             step 70 / 66 / 61; 276 k: 12.3 / 14.2 / 15.2
+//   width 3   68 k rows FP32 step best at 2; 104 k: bfloat16 step
+//             12.1 / 8.5 / 8.9, first step 11.7 / 8.4 / 8.3, K_gamma product
+//             11.6 / 9.1 / 9.0, B^T 7.8 / 6.8 / 6.4; 251 k: 14.2 / 12.7 /
+//             16.6, 13.6 / 12.9 / 14.6, 15.1 / 13.8 / 14.4, 10.1 / 10.4 /
+//             10.2; 493 k: 22.1 / 20.2 / 26.1, 20.5 / 20.8 / 23.4, 23.0 /
+//             22.3 / 23.7, 15.3 / 14.7 / 16.5; 2.05 M: 56 / 58 / 79,
+//             62 / 65 / 81, 72 / 71 / 73, 47 / 46 / 57
+inline int split_lg(int64_t rows, int G, int wg) {
+  if (G != 1 || !split_width(wg)) return 0;
+  if (rows < (int64_t(1) << 17) && rows * wg < (int64_t(1) << 18)) return 2;
+  return wg > 1 && rows < (int64_t(1) << 19) ? 1 : 0;
+}
+
+// The same for a product that ends in a sum over all rows (one partial per
+// workgroup, kMaxBlocks of them).
+inline int split_lg_dot(int64_t rows, int G, int wg) {
+  int lg = split_lg(rows, G, wg);
+  while (lg > 0 && grid_rows(rows, G, lg) > kMaxBlocks) --lg;
+  return lg;
+}
+
+// f(SP): the shared-slice variant of a kernel where lg > 0.
+template <int G, int WG, class F>
+void with_split(int lg, F&& f) {
+  if constexpr (G == 1 && split_width(WG)) {
+    if (lg > 0) return f(std::true_type{});
+  }
+  (void)lg;
+  f(std::false_type{});
+}
 
 // Lanes per row G of the velocity-row kernels: the largest of 8, 4, 2 not
 // above the request that divides W (the compiled variants).
@@ -142,9 +191,13 @@ inline int lanes_rows(stokes_ctx* c, int64_t nrows, int W, bool f32) {
 }
 
 template <int NS>
+void finish_n(stokes_ctx* c, int nblocks, int kind, int W, Scalars* sc, int cps, int nsys, int first, double* res) {
+  hipLaunchKernelGGL((k_finish<NS>), dim3(1), dim3(kBlock), 0, c->stream, (const double*)partials(c), nblocks, kind, W,
+                     sc, cps, nsys, first, res);
+}
+template <int NS>
 void finish(stokes_ctx* c, int64_t rows, int kind, int W, Scalars* sc, int cps, int nsys, int first, double* res) {
-  hipLaunchKernelGGL((k_finish<NS>), dim3(1), dim3(kBlock), 0, c->stream, (const double*)partials(c), grid_for(rows),
-                     kind, W, sc, cps, nsys, first, res);
+  finish_n<NS>(c, grid_for(rows), kind, W, sc, cps, nsys, first, res);
 }
 
 template <class T> const DevBuf& btvals(stokes_ctx* c);

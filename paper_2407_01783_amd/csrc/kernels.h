@@ -192,12 +192,34 @@ __device__ __forceinline__ int32_t sell_col_f(const SellIdx& ix, const SliceRef&
     return __builtin_nontemporal_load(ix.cols + r.beg + 64 * j);
 }
 
+// The share of a row's slots that one wavefront takes when 2^lg wavefronts of
+// a workgroup share a slice (rows_split below): part 0 .. 2^lg - 1.
+struct RowPart {
+  int part = 0, lg = 0;
+};
+
+// slots per interleaved group for values of type TM
+template <typename TM>
+constexpr int il_width() {
+  return sizeof(TM) == 2 ? 8 : 4;
+}
+
+// slots [a, b) of part p of a row of `width`: runs of whole groups of IW, the
+// rest of the row in the last part (the interleaved forms split the same way,
+// so that both sum a row alike)
+template <int IW>
+__device__ __forceinline__ void part_range(int width, RowPart p, int& a, int& b) {
+  const int ng = width / IW;
+  a = IW * ((ng * p.part) >> p.lg);
+  b = p.part == (1 << p.lg) - 1 ? width : IW * ((ng * (p.part + 1)) >> p.lg);
+}
+
 // acc += sum_j v_j x[c_j][sub W/G ...]; DS: v_j is multiplied by ds[c_j]
 // Groups of U entries, then groups of 4 (U > 4) and single entries for the
 // rest of the row, so short rows keep several loads in flight too.
 template <typename T, int W, int G, typename TM, int F, bool DS, int U = 4>
 __device__ __forceinline__ void sell_row_impl(const SellIdx& ix, const SliceRef& r, const TM* __restrict__ vals,
-                                              const T* __restrict__ xs, const T* __restrict__ ds,
+                                              const T* __restrict__ xs, const T* __restrict__ ds, RowPart part,
                                               T (&acc)[W / G]) {
   constexpr int WG = W / G;
   auto group = [&](auto Uc, int j) {
@@ -223,11 +245,12 @@ __device__ __forceinline__ void sell_row_impl(const SellIdx& ix, const SliceRef&
 #pragma unroll
       for (int w = 0; w < WG; ++w) acc[w] = fma(v[u], xv[u][w], acc[w]);
   };
-  int j = 0;
-  for (; j + U <= r.width; j += U) group(std::integral_constant<int, U>{}, j);
+  int j, end;
+  part_range<il_width<TM>()>(r.width, part, j, end);
+  for (; j + U <= end; j += U) group(std::integral_constant<int, U>{}, j);
   if constexpr (U > 4)
-    for (; j + 4 <= r.width; j += 4) group(std::integral_constant<int, 4>{}, j);
-  for (; j < r.width; ++j) group(std::integral_constant<int, 1>{}, j);
+    for (; j + 4 <= end; j += 4) group(std::integral_constant<int, 4>{}, j);
+  for (; j < end; ++j) group(std::integral_constant<int, 1>{}, j);
 }
 
 // TM is the storage type of the values (T, or _Float16 for a scaled copy);
@@ -235,17 +258,18 @@ __device__ __forceinline__ void sell_row_impl(const SellIdx& ix, const SliceRef&
 // values (S D), gathered at the columns.  U: entries per unrolled group.
 template <typename T, int W, int G = 1, typename TM = T, int U = 4>
 __device__ __forceinline__ void sell_row(const SellIdx& ix, const TM* __restrict__ vals, const T* __restrict__ x,
-                                         int64_t row, int sub, T (&acc)[W / G], const T* __restrict__ ds = nullptr) {
+                                         int64_t row, int sub, T (&acc)[W / G], const T* __restrict__ ds = nullptr,
+                                         RowPart part = {}) {
   const SliceRef r = slice_ref(ix, row);
   const T* __restrict__ xs = x + sub * (W / G);
   if (ds) {
-    if (r.af) sell_row_impl<T, W, G, TM, 2, true, U>(ix, r, vals, xs, ds, acc);
-    else if (r.pk) sell_row_impl<T, W, G, TM, 1, true, U>(ix, r, vals, xs, ds, acc);
-    else sell_row_impl<T, W, G, TM, 0, true, U>(ix, r, vals, xs, ds, acc);
+    if (r.af) sell_row_impl<T, W, G, TM, 2, true, U>(ix, r, vals, xs, ds, part, acc);
+    else if (r.pk) sell_row_impl<T, W, G, TM, 1, true, U>(ix, r, vals, xs, ds, part, acc);
+    else sell_row_impl<T, W, G, TM, 0, true, U>(ix, r, vals, xs, ds, part, acc);
   } else {
-    if (r.af) sell_row_impl<T, W, G, TM, 2, false, U>(ix, r, vals, xs, ds, acc);
-    else if (r.pk) sell_row_impl<T, W, G, TM, 1, false, U>(ix, r, vals, xs, ds, acc);
-    else sell_row_impl<T, W, G, TM, 0, false, U>(ix, r, vals, xs, ds, acc);
+    if (r.af) sell_row_impl<T, W, G, TM, 2, false, U>(ix, r, vals, xs, ds, part, acc);
+    else if (r.pk) sell_row_impl<T, W, G, TM, 1, false, U>(ix, r, vals, xs, ds, part, acc);
+    else sell_row_impl<T, W, G, TM, 0, false, U>(ix, r, vals, xs, ds, part, acc);
   }
 }
 
@@ -266,12 +290,6 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4a8_t __attribute__((ext_vector_type(4), aligned(8)));  // 16 bytes at 8-byte alignment
-
-// slots per interleaved group for values of type TM
-template <typename TM>
-constexpr int il_width() {
-  return sizeof(TM) == 2 ? 8 : 4;
-}
 
 __device__ __forceinline__ float half_bits(uint32_t h) {
   return (float)__builtin_bit_cast(_Float16, static_cast<uint16_t>(h));
@@ -343,11 +361,12 @@ __device__ __forceinline__ void load_cols(const SellIdx& ix, const SliceRef& r, 
 // eight entries in flight per lane.
 template <typename T, int W, int G, typename TM, int F>
 __device__ __forceinline__ void sell_row_il_impl(const SellIdx& ix, const SliceRef& r, const TM* __restrict__ vals,
-                                                 const T* __restrict__ x, int off, T (&acc)[W / G]) {
+                                                 const T* __restrict__ x, int off, RowPart part, T (&acc)[W / G]) {
   constexpr int WG = W / G, IW = il_width<TM>(), HG = 8 / IW;
   const int64_t s0 = r.eb << 6;
   const int lr = static_cast<int>(r.beg - s0);
-  const int gi = r.width / IW;
+  const int ng = r.width / IW;               // whole groups of the row
+  const int gi = (ng * (part.part + 1)) >> part.lg;  // end of this part's run of them
   auto groups = [&](auto Hc, int g) {
     constexpr int H = decltype(Hc)::value;
     int32_t c[H][IW];
@@ -372,12 +391,13 @@ __device__ __forceinline__ void sell_row_il_impl(const SellIdx& ix, const SliceR
 #pragma unroll
         for (int w = 0; w < WG; ++w) acc[w] = fma(v[h][k], xv[h][k][w], acc[w]);
   };
-  int g = 0;
+  int g = (ng * part.part) >> part.lg;
   for (; g + HG <= gi; g += HG) groups(std::integral_constant<int, HG>{}, g);
-  // the last group (if any) and the width mod IW tail slots (slot-major) in
-  // one round trip: every load first, then the sums in slot order
+  // the last group (if any) and (last part) the width mod IW tail slots
+  // (slot-major) in one round trip: every load first, then the sums in slot
+  // order
   const bool last = g < gi;
-  const int t = r.width - IW * gi;
+  const int t = gi == ng && part.part == (1 << part.lg) - 1 ? r.width - IW * ng : 0;
   if (!last && t == 0) return;
   int32_t c[IW], ct[IW - 1];
   T v[IW], vt[IW - 1];
@@ -389,8 +409,8 @@ __device__ __forceinline__ void sell_row_il_impl(const SellIdx& ix, const SliceR
 #pragma unroll
   for (int k = 0; k < IW - 1; ++k)
     if (k < t) {
-      ct[k] = sell_col_f<F>(ix, r, IW * gi + k);
-      vt[k] = (T)__builtin_nontemporal_load(vals + r.beg + 64 * (IW * gi + k));
+      ct[k] = sell_col_f<F>(ix, r, IW * ng + k);
+      vt[k] = (T)__builtin_nontemporal_load(vals + r.beg + 64 * (IW * ng + k));
     }
   T xv[IW][WG], xt[IW - 1][WG];
   if (last)
@@ -417,12 +437,12 @@ __device__ __forceinline__ void sell_row_il_impl(const SellIdx& ix, const SliceR
 
 template <typename T, int W, int G, typename TM>
 __device__ __forceinline__ void sell_row_il(const SellIdx& ix, const TM* __restrict__ vals, const T* __restrict__ x,
-                                            int64_t row, int sub, T (&acc)[W / G]) {
+                                            int64_t row, int sub, T (&acc)[W / G], RowPart part = {}) {
   const SliceRef r = slice_ref(ix, row);
   const int off = sub * (W / G);
-  if (r.af) sell_row_il_impl<T, W, G, TM, 2>(ix, r, vals, x, off, acc);
-  else if (r.pk) sell_row_il_impl<T, W, G, TM, 1>(ix, r, vals, x, off, acc);
-  else sell_row_il_impl<T, W, G, TM, 0>(ix, r, vals, x, off, acc);
+  if (r.af) sell_row_il_impl<T, W, G, TM, 2>(ix, r, vals, x, off, part, acc);
+  else if (r.pk) sell_row_il_impl<T, W, G, TM, 1>(ix, r, vals, x, off, part, acc);
+  else sell_row_il_impl<T, W, G, TM, 0>(ix, r, vals, x, off, part, acc);
 }
 
 // B rows (pressure vertex): acc[r] = sum_j sum_c B^c_j u[col_j][r][c] over the
@@ -491,7 +511,8 @@ __device__ __forceinline__ T plane(const T (&b)[D], int d) {
 // of the W = D NRB outputs (component w is rhs w / D, plane w mod D).
 template <typename T, int D, int NRB, int G, int F>
 __device__ __forceinline__ void sell_row_Bt_impl(const SellIdx& ix, const SliceRef& rf, const T* __restrict__ vals,
-                                                 const T* __restrict__ p, int sub, T (&acc)[D * NRB / G]) {
+                                                 const T* __restrict__ p, int sub, RowPart part,
+                                                 T (&acc)[D * NRB / G]) {
   constexpr int WG = D * NRB / G;
   int rr[WG], dd[WG];
 #pragma unroll
@@ -500,8 +521,9 @@ __device__ __forceinline__ void sell_row_Bt_impl(const SellIdx& ix, const SliceR
     dd[w] = (sub * WG + w) - rr[w] * D;
   }
   constexpr int U = 4;
-  int j = 0;
-  for (; j + U <= rf.width; j += U) {
+  int j, end;
+  part_range<U>(rf.width, part, j, end);
+  for (; j + U <= end; j += U) {
     int32_t c[U];
     T b[U][D], pv[U][WG];
 #pragma unroll
@@ -520,7 +542,7 @@ __device__ __forceinline__ void sell_row_Bt_impl(const SellIdx& ix, const SliceR
 #pragma unroll
       for (int w = 0; w < WG; ++w) acc[w] = fma(G == 1 ? b[q][w % D] : plane<T, D>(b[q], dd[w]), pv[q][w], acc[w]);
   }
-  for (; j < rf.width; ++j) {
+  for (; j < end; ++j) {
     const int64_t k = rf.beg + 64 * j;
     const int32_t c = sell_col_f<F>(ix, rf, j);
     T b[D];
@@ -534,11 +556,11 @@ __device__ __forceinline__ void sell_row_Bt_impl(const SellIdx& ix, const SliceR
 
 template <typename T, int D, int NRB, int G = 1>
 __device__ __forceinline__ void sell_row_Bt(const SellIdx& ix, const T* __restrict__ vals, const T* __restrict__ p,
-                                            int64_t row, int sub, T (&acc)[D * NRB / G]) {
+                                            int64_t row, int sub, T (&acc)[D * NRB / G], RowPart part = {}) {
   const SliceRef rf = slice_ref(ix, row);
-  if (rf.af) sell_row_Bt_impl<T, D, NRB, G, 2>(ix, rf, vals, p, sub, acc);
-  else if (rf.pk) sell_row_Bt_impl<T, D, NRB, G, 1>(ix, rf, vals, p, sub, acc);
-  else sell_row_Bt_impl<T, D, NRB, G, 0>(ix, rf, vals, p, sub, acc);
+  if (rf.af) sell_row_Bt_impl<T, D, NRB, G, 2>(ix, rf, vals, p, sub, part, acc);
+  else if (rf.pk) sell_row_Bt_impl<T, D, NRB, G, 1>(ix, rf, vals, p, sub, part, acc);
+  else sell_row_Bt_impl<T, D, NRB, G, 0>(ix, rf, vals, p, sub, part, acc);
 }
 
 #define GRID_STRIDE_ROWS(row, nrows)                                                      \
@@ -569,6 +591,78 @@ __device__ __forceinline__ void sell_row_Bt(const SellIdx& ix, const T* __restri
 
 #define XCD_ROWS(row, nrows, PERM) XCD_ROWS_G(row, sub_unused_ [[maybe_unused]], nrows, 1, PERM)
 
+// Widths whose rows may be shared (split_lg in dispatch.h says why these).
+__host__ __device__ constexpr bool split_width(int wg) { return wg == 1 || wg == 3; }
+
+// The XCD row partition as a function, for products whose rows may be shared
+// by wavefronts: with lg > 0 the 2^lg wavefronts of a workgroup that share a
+// slice each take a run of its slots (RowPart), their sums meet in the LDS and
+// the first of them finishes the row.  A mesh of a few tens of cells has at
+// most a few wavefronts' worth of rows per SIMD, so a product lasts as long as
+// its longest row's chain of loads and gathers; sharing the slice cuts that
+// chain, and, unlike lanes sharing a row, keeps every load as wide as before
+// and the slot words scalar.  lg by the launcher (split_lg in dispatch.h).
+//   prod(row, sub, part, acc): acc += the part's sum;  epi(row, sub, acc)
+// SP: lg > 0 (a variant of its own: the other would lose a wavefront per SIMD
+// to its registers).  One pass: the grid covers every row (grid_rows in
+// dispatch.h).  LOOP: a capped grid strides over the rows instead, without SP.
+// (No loop runs around the barrier: past a barrier the compiler would read the
+// slot words with vector loads, which costs the velocity step a quarter.)
+template <int G, int WG, typename T, bool LOOP, bool SP, class Prod, class Epi>
+__device__ __forceinline__ void rows_split(int64_t nrows, const int32_t* perm, int lg, Prod&& prod, Epi&& epi) {
+  static_assert(!SP || (G == 1 && split_width(WG)), "one lane per row, narrow rows");
+  const int64_t nx = (gridDim.x % 8 == 0) ? gridDim.x / 8 : gridDim.x;
+  const int64_t xx = (gridDim.x % 8 == 0) ? blockIdx.x % 8 : 0;
+  const int64_t xi = (gridDim.x % 8 == 0) ? blockIdx.x / 8 : blockIdx.x;
+  const int64_t xn = (gridDim.x % 8 == 0) ? ((nrows + 7) / 8 + 63) / 64 * 64 : nrows;
+  const int64_t xb = xx * xn;
+  const int64_t xe = xb + xn < nrows ? xb + xn : nrows;
+  const int sub = (int)(threadIdx.x % G);
+  auto natural = [&](int64_t r) {
+    return perm ? ((int64_t)perm[__builtin_amdgcn_readfirstlane((int)(r >> 6))] << 6) + (r & 63) : r;
+  };
+  auto whole = [&](int64_t r) {
+    const int64_t row = natural(r);
+    T acc[WG];
+#pragma unroll
+    for (int w = 0; w < WG; ++w) acc[w] = 0;
+    prod(row, sub, RowPart{}, acc);
+    epi(row, sub, acc);
+  };
+  if constexpr (SP) {
+    __shared__ T sums[3 * 64 * WG];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int slice = wave >> lg, base = slice * ((1 << lg) - 1);
+    RowPart part;
+    part.lg = lg;
+    part.part = wave & ((1 << lg) - 1);
+    const int64_t r = xb + xi * (kBlock >> lg) + slice * 64 + lane;
+    const int64_t row = r < xe ? natural(r) : r;
+    T acc[WG];
+#pragma unroll
+    for (int w = 0; w < WG; ++w) acc[w] = 0;
+    if (r < xe) prod(row, sub, part, acc);
+    if (part.part > 0) {
+#pragma unroll
+      for (int w = 0; w < WG; ++w) sums[((base + part.part - 1) * WG + w) * 64 + lane] = acc[w];
+    }
+    __syncthreads();
+    if (part.part == 0 && r < xe) {
+      for (int q = 0; q < (1 << lg) - 1; ++q)
+#pragma unroll
+        for (int w = 0; w < WG; ++w) acc[w] += sums[((base + q) * WG + w) * 64 + lane];
+      epi(row, sub, acc);
+    }
+    return;
+  }
+  if constexpr (LOOP) {
+    for (int64_t r = xb + (xi * kBlock + threadIdx.x) / G; r < xe; r += nx * kBlock / G) whole(r);
+  } else {
+    const int64_t r = xb + (xi * kBlock + threadIdx.x) / G;
+    if (r < xe) whole(r);
+  }
+}
+
 // Row-group mapping without the XCD partition (streaming kernels).
 #define GRID_STRIDE_ROWS_G(row, sub, nrows, G)                                             \
   const int sub = (int)(threadIdx.x % (G));                                               \
@@ -588,16 +682,15 @@ __device__ __forceinline__ void expand_parts(const double (&pg)[W / G], int sub,
 
 // y = a * (S x) + b * yin   (yin may alias y; ignored when b == 0)
 // IL: ix and vals are the interleaved copies.
-template <typename T, int W, int G, typename TM = T, bool IL = false>
+template <typename T, int W, int G, typename TM = T, bool IL = false, bool SP = false>
 __global__ __launch_bounds__(kBlock) void k_spmv(int64_t nrows, SellIdx ix, const TM* __restrict__ vals,
-                                                 const T* __restrict__ x, T* y, T a, const T* yin, T b) {
+                                                 const T* __restrict__ x, T* y, T a, const T* yin, T b, int lg) {
   constexpr int WG = W / G;
-  XCD_ROWS_G(row, sub, nrows, G, ix.rperm) {
-    T acc[WG];
-#pragma unroll
-    for (int w = 0; w < WG; ++w) acc[w] = 0;
-    if constexpr (IL) sell_row_il<T, W, G, TM>(ix, vals, x, row, sub, acc);
-    else sell_row<T, W, G, TM, (W / G == 1 ? 16 : W / G <= 2 ? 8 : 4)>(ix, vals, x, row, sub, acc);
+  auto prod = [&](int64_t row, int sub, RowPart part, T(&acc)[WG]) {
+    if constexpr (IL) sell_row_il<T, W, G, TM>(ix, vals, x, row, sub, acc, part);
+    else sell_row<T, W, G, TM, (W / G == 1 ? 16 : W / G <= 2 ? 8 : 4)>(ix, vals, x, row, sub, acc, nullptr, part);
+  };
+  auto epi = [&](int64_t row, int sub, T(&acc)[WG]) {
     const int64_t o = row * W + sub * WG;
     // yin may alias y: every load of the row is issued before its stores
     T yi[WG];
@@ -605,7 +698,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv(int64_t nrows, SellIdx ix, cons
     for (int w = 0; w < WG; ++w) yi[w] = b != T(0) ? yin[o + w] : T(0);
 #pragma unroll
     for (int w = 0; w < WG; ++w) y[o + w] = fma(b, yi[w], a * acc[w]);
-  }
+  };
+  rows_split<G, WG, T, false, SP>(nrows, ix.rperm, lg, prod, epi);
 }
 
 // ------------------------------------------------ entry-split SELL rows
@@ -750,11 +844,11 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step_es(int64_t nrows, SellIdx 
 
 // CG direction step with the product folded in:
 //   q = S z (+ extra) + beta q,  p = z + beta p,  sigma = p . q  -> alpha
-template <typename T, int W, int G>
+template <typename T, int W, int G, bool SP = false>
 __global__ __launch_bounds__(kBlock) void k_cg_spmv(int64_t nrows, SellIdx ix,
                                                     const T* __restrict__ vals, const T* __restrict__ z,
                                                     const T* __restrict__ extra, T* __restrict__ q,
-                                                    T* __restrict__ p, Scalars* sc, int cps, int nsys, double* partials) {
+                                                    T* __restrict__ p, Scalars* sc, int cps, int nsys, double* partials, int lg) {
   constexpr int WG = W / G;
   const int sub0 = (int)(threadIdx.x % G);
   T beta[WG];
@@ -763,11 +857,10 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(int64_t nrows, SellIdx ix,
   double part[WG];
 #pragma unroll
   for (int w = 0; w < WG; ++w) part[w] = 0;
-  XCD_ROWS_G(row, sub, nrows, G, ix.rperm) {
-    T acc[WG];
-#pragma unroll
-    for (int w = 0; w < WG; ++w) acc[w] = 0;
-    if (ix.sp) sell_row<T, W, G>(ix, vals, z, row, sub, acc);
+  auto prod = [&](int64_t row, int sub, RowPart pt, T(&acc)[WG]) {
+    if (ix.sp) sell_row<T, W, G>(ix, vals, z, row, sub, acc, nullptr, pt);
+  };
+  auto epi = [&](int64_t row, int sub, T(&acc)[WG]) {
 #pragma unroll
     for (int w = 0; w < WG; ++w) {
       const int64_t i = row * W + sub * WG + w;
@@ -779,7 +872,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(int64_t nrows, SellIdx ix,
       p[i] = pn;
       part[w] += (double)pn * (double)qn;
     }
-  }
+  };
+  rows_split<G, WG, T, true, SP>(nrows, ix.rperm, lg, prod, epi);
   double pf[W];
   expand_parts<W, G>(part, sub0, pf);
   grid_reduce<W>(pf, partials);
@@ -855,22 +949,21 @@ __global__ __launch_bounds__(kBlock) void k_cheb_init(int64_t nrows, const T* __
 // One Chebyshev step (Saad, Iterative Methods, Alg. 12.1, three-term form):
 //   res = res_in - S d ;  dn = c1 d + c2 dinv res ;  z += dn
 // DOT: also rho = rvec . z -> beta (CG preconditioner use), first => beta = 0.
-template <typename T, int W, int DOT, int G, typename TM = T>
+template <typename T, int W, int DOT, int G, typename TM = T, bool SP = false>
 __global__ __launch_bounds__(kBlock) void k_cheb_step(int64_t nrows, SellIdx ix,
                                                       const TM* __restrict__ vals, T ms, const T* __restrict__ d,
                                                       T* __restrict__ dn, const T* res_in, T* res_out,
                                                       T* __restrict__ z, const T* __restrict__ dinv, T c1, T c2,
                                                       const T* __restrict__ rvec, Scalars* sc, int cps, int nsys,
-                                                      int first, double* partials) {
+                                                      int first, double* partials, int lg) {
   constexpr int WG = W / G;
   double part[WG];
 #pragma unroll
   for (int w = 0; w < WG; ++w) part[w] = 0;
-  XCD_ROWS_G(row, sub, nrows, G, ix.rperm) {
-    T acc[WG];
-#pragma unroll
-    for (int w = 0; w < WG; ++w) acc[w] = 0;
-    sell_row<T, W, G, TM, (W / G == 1 ? 16 : W / G <= 2 ? 8 : 4)>(ix, vals, d, row, sub, acc);
+  auto prod = [&](int64_t row, int sub, RowPart pt, T(&acc)[WG]) {
+    sell_row<T, W, G, TM, (W / G == 1 ? 16 : W / G <= 2 ? 8 : 4)>(ix, vals, d, row, sub, acc, nullptr, pt);
+  };
+  auto epi = [&](int64_t row, int sub, T(&acc)[WG]) {
     const T di = c2 * dinv[row];
     const int64_t o = row * W + sub * WG;
     // res_in may alias res_out: load the whole row before any store
@@ -891,7 +984,8 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step(int64_t nrows, SellIdx ix,
       z[o + w] = zn;
       if (DOT) part[w] += (double)rvec[o + w] * (double)zn;
     }
-  }
+  };
+  rows_split<G, WG, T, DOT != 0, SP>(nrows, ix.rperm, lg, prod, epi);
   if (DOT) {
     double pf[W];
     expand_parts<W, G>(part, (int)(threadIdx.x % G), pf);
@@ -904,17 +998,16 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step(int64_t nrows, SellIdx ix,
 //   res = r - S d0 ;  d1 = c1 d0 + c2 dinv res ;  z = d0 + d1
 // ACC: z += d0 + d1 (z holds a previous approximation) instead of z = d0 + d1
 // SC: vals already hold S_ij dinv_j (no gather of dinv at the columns).
-template <typename T, int W, int ACC, int G, int SC, typename TM = T>
+template <typename T, int W, int ACC, int G, int SC, typename TM = T, bool SP = false>
 __global__ __launch_bounds__(kBlock) void k_cheb_first(int64_t nrows, SellIdx ix, const TM* __restrict__ vals, T ms,
                                                        const T* __restrict__ r, const T* __restrict__ dinv, T theta_inv,
                                                        T* __restrict__ d1, T* __restrict__ res, T* __restrict__ z,
-                                                       T c1, T c2) {
+                                                       T c1, T c2, int lg) {
   constexpr int WG = W / G;
-  XCD_ROWS_G(row, sub, nrows, G, ix.rperm) {
-    T acc[WG];
-#pragma unroll
-    for (int w = 0; w < WG; ++w) acc[w] = 0;
-    sell_row<T, W, G, TM, (W / G == 1 ? 16 : W / G <= 2 ? 8 : 4)>(ix, vals, r, row, sub, acc, SC ? nullptr : dinv);
+  auto prod = [&](int64_t row, int sub, RowPart pt, T(&acc)[WG]) {
+    sell_row<T, W, G, TM, (W / G == 1 ? 16 : W / G <= 2 ? 8 : 4)>(ix, vals, r, row, sub, acc, SC ? nullptr : dinv, pt);
+  };
+  auto epi = [&](int64_t row, int sub, T(&acc)[WG]) {
     const T di = dinv[row];
     const int64_t o = row * W + sub * WG;
 #pragma unroll
@@ -927,7 +1020,8 @@ __global__ __launch_bounds__(kBlock) void k_cheb_first(int64_t nrows, SellIdx ix
       d1[i] = dnv;
       z[i] = ACC ? z[i] + (d0 + dnv) : d0 + dnv;
     }
-  }
+  };
+  rows_split<G, WG, T, false, SP>(nrows, ix.rperm, lg, prod, epi);
 }
 
 // Chebyshev steps on the column-scaled operator S D^{-1} held as TM (the
@@ -1069,7 +1163,8 @@ __device__ __forceinline__ float bf_word(uint32_t u, int hi) {
 
 template <int W, int G, typename TM, int F, int U>
 __device__ __forceinline__ void sell_row_bq_impl(const SellIdx& ix, const SliceRef& r, const TM* __restrict__ vals,
-                                                 const uint16_t* __restrict__ xq, int off, float (&acc)[W / G]) {
+                                                 const uint16_t* __restrict__ xq, int off, RowPart part,
+                                                 float (&acc)[W / G]) {
   constexpr int WG = W / G, WP = bf_width<W>();
   using Raw = BfRaw<WP, WG>;
   auto group = [&](auto Uc, int j) {
@@ -1099,11 +1194,12 @@ __device__ __forceinline__ void sell_row_bq_impl(const SellIdx& ix, const SliceR
         for (int w = 0; w < WG; ++w) acc[w] = fma(v[u], xv[u][w], acc[w]);
     }
   };
-  int j = 0;
-  for (; j + U <= r.width; j += U) group(std::integral_constant<int, U>{}, j);
+  int j, end;
+  part_range<il_width<TM>()>(r.width, part, j, end);
+  for (; j + U <= end; j += U) group(std::integral_constant<int, U>{}, j);
   if constexpr (U > 4)
-    for (; j + 4 <= r.width; j += 4) group(std::integral_constant<int, 4>{}, j);
-  for (; j < r.width; ++j) group(std::integral_constant<int, 1>{}, j);
+    for (; j + 4 <= end; j += 4) group(std::integral_constant<int, 4>{}, j);
+  for (; j < end; ++j) group(std::integral_constant<int, 1>{}, j);
 }
 
 // The bfloat16-direction row over the interleaved half-precision copies
@@ -1111,13 +1207,15 @@ __device__ __forceinline__ void sell_row_bq_impl(const SellIdx& ix, const SliceR
 template <int W, int G, int F>
 __device__ __forceinline__ void sell_row_bq_il_impl(const SellIdx& ix, const SliceRef& r,
                                                   const _Float16* __restrict__ vals,
-                                                  const uint16_t* __restrict__ xq, int off, float (&acc)[W / G]) {
+                                                  const uint16_t* __restrict__ xq, int off, RowPart part,
+                                                  float (&acc)[W / G]) {
   constexpr int WG = W / G, WP = bf_width<W>(), IW = il_width<_Float16>();
   using Raw = BfRaw<WP, WG>;
   static_assert(Raw::kOn, "interleaved rows take the packed bfloat16 gathers");
   const int64_t s0 = r.eb << 6;
   const int lr = static_cast<int>(r.beg - s0);
-  const int gi = r.width / IW;
+  const int ng = r.width / IW;                       // whole groups of the row
+  const int gi = (ng * (part.part + 1)) >> part.lg;  // end of this part's run of them
   auto entry = [&](int g) { return s0 + 64 * IW * (int64_t)g + IW * lr; };
   // H groups at a time: values and offsets first, then all their gathers
   auto groups = [&](auto Hc, int g) {
@@ -1143,7 +1241,7 @@ __device__ __forceinline__ void sell_row_bq_il_impl(const SellIdx& ix, const Sli
   };
   // narrow lanes keep two groups (16 entries) in flight, wide ones one
   constexpr int HG = WG <= 4 ? 2 : 1;
-  int g = 0;
+  int g = (ng * part.part) >> part.lg;
   if constexpr (F == 2 && WP == 4 && WG >= 3) {
     // 8-byte rows: the leading pair sub-groups (four slots 4p .. 4p+3 of
     // which slots 4p, 4p+1 and 4p+2, 4p+3 gather adjacent nodes in every
@@ -1184,15 +1282,17 @@ __device__ __forceinline__ void sell_row_bq_il_impl(const SellIdx& ix, const Sli
           for (int w = 0; w < WG; ++w) acc[w] = fma(v[h][k], bf_word(xr[h][k][w / 2], w & 1), acc[w]);
       }
     };
-    const int gp = r.pg / 2;  // groups made of four pairs
+    const int gp = min(r.pg / 2, gi);  // end of the groups made of four pairs
     for (; g + 2 <= gp; g += 2) pairs(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{}, g);
     for (; g < gp; ++g) pairs(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, g);
-    if ((r.pg & 1) && g < gi) pairs(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{}, g++);
+    if ((r.pg & 1) && g == r.pg / 2 && g < gi)
+      pairs(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{}, g++);
   }
   for (; g + HG <= gi; g += HG) groups(std::integral_constant<int, HG>{}, g);
   if (g < gi) groups(std::integral_constant<int, 1>{}, g);
-  // the remaining width mod IW slots, slot-major
-  for (int j = IW * gi; j < r.width; ++j) {
+  // (last part) the remaining width mod IW slots, slot-major
+  if (part.part != (1 << part.lg) - 1) return;
+  for (int j = IW * ng; j < r.width; ++j) {
     const int32_t c = sell_col_f<F>(ix, r, j);
     const float v = (float)__builtin_nontemporal_load(vals + r.beg + 64 * j);
     uint32_t xr[Raw::kWords];
@@ -1234,19 +1334,18 @@ struct QSum {
 // res = r - (S D^{-1}) q0, q1 = bf16(c1 q0 + c2 res), z (+)= dinv (q0 + q1);
 // ACC = 2 leaves z to the closing step (no z, no dinv).
 // IL: ix and vals are the interleaved copies.
-template <typename TM, int W, int ACC, int G, int U = 8, bool IL = false>
+template <typename TM, int W, int ACC, int G, int U = 8, bool IL = false, bool SP = false>
 __global__ __launch_bounds__(kBlock) void k_cheb_first_qb(int64_t nrows, SellIdx ix, const TM* __restrict__ vals,
                                                           const float* __restrict__ r, const float* __restrict__ dinv,
                                                           float theta_inv, uint16_t* __restrict__ q1,
                                                           float* __restrict__ res, float* __restrict__ z, float c1,
-                                                          float c2) {
+                                                          float c2, int lg) {
   constexpr int WG = W / G, WP = bf_width<W>();
-  XCD_ROWS_G(row, sub, nrows, G, ix.rperm) {
-    float acc[WG];
-#pragma unroll
-    for (int w = 0; w < WG; ++w) acc[w] = 0;
-    if constexpr (IL) sell_row_il<float, W, G, TM>(ix, vals, r, row, sub, acc);
-    else sell_row<float, W, G, TM, (W / G >= 8 ? 4 : U)>(ix, vals, r, row, sub, acc);
+  auto prod = [&](int64_t row, int sub, RowPart pt, float(&acc)[WG]) {
+    if constexpr (IL) sell_row_il<float, W, G, TM>(ix, vals, r, row, sub, acc, pt);
+    else sell_row<float, W, G, TM, (W / G >= 8 ? 4 : U)>(ix, vals, r, row, sub, acc, nullptr, pt);
+  };
+  auto epi = [&](int64_t row, int sub, float(&acc)[WG]) {
     const float di = ACC == 2 ? 0.f : dinv[row];
     const int64_t o = row * W + sub * WG, oq = row * WP + sub * WG;
 #pragma unroll
@@ -1264,7 +1363,8 @@ __global__ __launch_bounds__(kBlock) void k_cheb_first_qb(int64_t nrows, SellIdx
     if constexpr (WP != W) {
       if (sub == G - 1) q1[row * WP + W] = 0;
     }
-  }
+  };
+  rows_split<G, WG, float, false, SP>(nrows, ix.rperm, lg, prod, epi);
 }
 
 // Later steps:  res = res_in - (S D^{-1}) q ;  qn = bf16(c1 q + c2 res) ;  z += dinv qn
@@ -1272,33 +1372,30 @@ __global__ __launch_bounds__(kBlock) void k_cheb_first_qb(int64_t nrows, SellIdx
 // neither res nor qn is stored, z = dinv (fin.theta_inv fin.r + fin.q[0] +
 // ... + fin.q[n-1] + qn).
 // IL: ix.cdel / ix.cols and vals are the interleaved copies.
-template <typename TM, int W, int G, int U = 8, bool IL = false, int ZM = 0>
+template <typename TM, int W, int G, int U = 8, bool IL = false, int ZM = 0, bool SP = false>
 __global__ __launch_bounds__(kBlock) void k_cheb_step_qb(int64_t nrows, SellIdx ix, const TM* __restrict__ vals,
                                                          const uint16_t* __restrict__ q, uint16_t* __restrict__ qn,
                                                          const float* res_in, float* res_out, float* __restrict__ z,
                                                          const float* __restrict__ dinv, float c1, float c2,
-                                                         QSum fin) {
+                                                         QSum fin, int lg) {
   constexpr int WG = W / G, WP = bf_width<W>();
-  XCD_ROWS_G(row, sub, nrows, G, ix.rperm) {
-    const int64_t o = row * W + sub * WG;
-    float acc[WG];
-#pragma unroll
-    for (int w = 0; w < WG; ++w) acc[w] = 0;
-    {
-      const SliceRef rf = slice_ref(ix, row);
-      // wide lanes (8 or more components) take four entries per group: with
-      // eight, the gathered words alone hold most of the registers
-      constexpr int UB = WG >= 8 ? 4 : U;
-      if constexpr (IL) {
-        if (rf.af) sell_row_bq_il_impl<W, G, 2>(ix, rf, vals, q, sub * WG, acc);
-        else if (rf.pk) sell_row_bq_il_impl<W, G, 1>(ix, rf, vals, q, sub * WG, acc);
-        else sell_row_bq_il_impl<W, G, 0>(ix, rf, vals, q, sub * WG, acc);
-      } else {
-        if (rf.af) sell_row_bq_impl<W, G, TM, 2, UB>(ix, rf, vals, q, sub * WG, acc);
-        else if (rf.pk) sell_row_bq_impl<W, G, TM, 1, UB>(ix, rf, vals, q, sub * WG, acc);
-        else sell_row_bq_impl<W, G, TM, 0, UB>(ix, rf, vals, q, sub * WG, acc);
-      }
+  auto prod = [&](int64_t row, int sub, RowPart pt, float(&acc)[WG]) {
+    const SliceRef rf = slice_ref(ix, row);
+    // wide lanes (8 or more components) take four entries per group: with
+    // eight, the gathered words alone hold most of the registers
+    constexpr int UB = WG >= 8 ? 4 : U;
+    if constexpr (IL) {
+      if (rf.af) sell_row_bq_il_impl<W, G, 2>(ix, rf, vals, q, sub * WG, pt, acc);
+      else if (rf.pk) sell_row_bq_il_impl<W, G, 1>(ix, rf, vals, q, sub * WG, pt, acc);
+      else sell_row_bq_il_impl<W, G, 0>(ix, rf, vals, q, sub * WG, pt, acc);
+    } else {
+      if (rf.af) sell_row_bq_impl<W, G, TM, 2, UB>(ix, rf, vals, q, sub * WG, pt, acc);
+      else if (rf.pk) sell_row_bq_impl<W, G, TM, 1, UB>(ix, rf, vals, q, sub * WG, pt, acc);
+      else sell_row_bq_impl<W, G, TM, 0, UB>(ix, rf, vals, q, sub * WG, pt, acc);
     }
+  };
+  auto epi = [&](int64_t row, int sub, float(&acc)[WG]) {
+    const int64_t o = row * W + sub * WG;
     // res_in may alias res_out: load the whole row before any store
     float ri[WG], qq[WG], zz[WG];
     const float di = ZM == 1 ? 0.f : dinv[row];
@@ -1332,7 +1429,8 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step_qb(int64_t nrows, SellIdx 
     if constexpr (WP != W && ZM != 2) {
       if (sub == G - 1) qn[row * WP + W] = 0;
     }
-  }
+  };
+  rows_split<G, WG, float, false, SP>(nrows, ix.rperm, lg, prod, epi);
 }
 
 // ------------------------------------------------------------- B and B^T
@@ -1364,16 +1462,15 @@ __global__ __launch_bounds__(kBlock) void k_B(int64_t nrows, SellIdx ix, const T
 }
 
 // u = a * scale .* (B^T p) + b * uin     (scale per node, may be null)
-template <typename T, int D, int NRB, int G>
+template <typename T, int D, int NRB, int G, bool SP = false>
 __global__ __launch_bounds__(kBlock) void k_Bt(int64_t nrows, SellIdx ix, const T* __restrict__ vals,
                                                const T* __restrict__ p, const T* __restrict__ scale, T* uout,
-                                               T a, const T* uin, T b, T* __restrict__ btout) {
+                                               T a, const T* uin, T b, T* __restrict__ btout, int lg) {
   constexpr int W = D * NRB, WG = W / G;
-  XCD_ROWS_G(row, sub, nrows, G, ix.rperm) {
-    T acc[WG];
-#pragma unroll
-    for (int w = 0; w < WG; ++w) acc[w] = 0;
-    sell_row_Bt<T, D, NRB, G>(ix, vals, p, row, sub, acc);
+  auto prod = [&](int64_t row, int sub, RowPart pt, T(&acc)[WG]) {
+    sell_row_Bt<T, D, NRB, G>(ix, vals, p, row, sub, acc, pt);
+  };
+  auto epi = [&](int64_t row, int sub, T(&acc)[WG]) {
     const T sc = scale ? a * scale[row] : a;
     const int64_t o = row * W + sub * WG;
     T ui[WG];  // uin may alias uout
@@ -1385,7 +1482,8 @@ __global__ __launch_bounds__(kBlock) void k_Bt(int64_t nrows, SellIdx ix, const 
 #pragma unroll
       for (int w = 0; w < WG; ++w) btout[o + w] = sc * acc[w];
     }
-  }
+  };
+  rows_split<G, WG, T, false, SP>(nrows, ix.rperm, lg, prod, epi);
 }
 
 // Momentum rows of the coupled operator:
