@@ -267,9 +267,11 @@ struct stokes_ctx {
   // 10,648 rows 85 / 165 us).  mg_dense_max, where the level could coarsen
   // further: smoothing, residuals and transfers of a level of some thousand
   // rows and the solve below it are ten launches of 4-5 us, 36 / 40 us.
+  // The P2 pressure level of a P3/P2 pair keeps its V-cycle from 1,500 rows on
+  // (mg_dense_p2; tests pin that cycle's contraction at 1,681 and 2,197 rows).
   // mg_dense_last, where it cannot (an odd cell count): the polynomial over
   // the whole spectrum is 24 launches, 100-140 / 150 us, and less exact.
-  int64_t mg_dense_max = 5000, mg_dense_last = 9000;
+  int64_t mg_dense_max = 5000, mg_dense_p2 = 1500, mg_dense_last = 9000;
   double mg_smooth_ratio = 10.0;
   int use_mgx = 1;                      // lumped CC: precondition with mgx (0: mgq)
   // P3/P2: build the Galerkin hierarchy too (0: only the eps M_Q + L_Q one),

@@ -276,7 +276,8 @@ void build_mg(stokes_ctx* c) {
   int n = fm.order == 3 ? 2 * fm.n : fm.n;  // lattice intervals per side of the pressure nodes
   H.lv.push_back({&c->sQ, &c->XQ64, &c->XQ32, &c->dXQ64, &c->dXQ32, &c->bXQ_smooth, &c->bXQ, n});
   // coarsen while the current level is too large for the dense coarse solve
-  while (n % 2 == 0 && n > 2 && ipow(n + 1, D) > c->mg_dense_max) {
+  auto dense_max = [&] { return fm.order == 3 && n == 2 * fm.n ? c->mg_dense_p2 : c->mg_dense_max; };
+  while (n % 2 == 0 && n > 2 && ipow(n + 1, D) > dense_max()) {
     n /= 2;
     const int stride = fm.n / n;  // mesh vertices per coarse cell side
     auto L = std::make_unique<MgLevel>();
