@@ -533,6 +533,15 @@ __global__ __launch_bounds__(kBlock) void k_scale_cols(int64_t n, const int32_t*
   }
 }
 
+// the half-precision copy alone
+__global__ __launch_bounds__(kBlock) void k_scale_cols_half(int64_t n, const int32_t* __restrict__ cols,
+                                                            const double* __restrict__ vals,
+                                                            const double* __restrict__ dinv,
+                                                            _Float16* __restrict__ out16) {
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+    out16[k] = (_Float16)(vals[k] * dinv[cols[k]]);
+}
+
 // rows of X = B_I Lambda_V^-1 B_I^T (lumped-mass pressure operator of Sec. 4.3),
 // one wavefront per P1 row k: each lane owns output entries (k, l) and merges
 // the sorted B rows k and l, summing over the shared interior P2 columns j
@@ -1719,6 +1728,9 @@ void upload_level(stokes_ctx* c, const HostCsr& A, const std::vector<double>& av
     L.s16 = static_cast<float>(amax);
     L.v16.alloc(L.S.nnz_pad * sizeof(_Float16));
     launch(c, L.S.nnz_pad, k_to_half, L.S.nnz_pad, L.v64.as<double>(), 1.0 / double(L.s16), L.v16.as<_Float16>());
+    L.vd16.alloc(L.S.nnz_pad * sizeof(_Float16));
+    launch(c, L.S.nnz_pad, k_scale_cols_half, L.S.nnz_pad, L.S.cols.as<int32_t>(), L.v64.as<double>(),
+           L.d64.as<double>(), L.vd16.as<_Float16>());
   }
   double lo, hi, g;
   lanczos_bounds(c, L.S, L.v64.as<double>(), L.d64.as<double>(), std::min<int>(40, (int)nr), lo, hi, g);
@@ -1779,7 +1791,7 @@ void assemble_galerkin(stokes_ctx* c, MgHier& H) {
     upload_level(c, A, av, *L);
     const bool p2 = c->mesh.order == 3 && H.lv.empty();  // the P2 pressure level of a P3/P2 pair
     if (p2) L->bs.lo = L->bs.hi / c->mgx_p2_ratio;
-    H.lv.push_back({&L->S, &L->v64, &L->v32, &L->d64, &L->d32, &L->bs, &L->bf, n, &L->v16, L->s16,
+    H.lv.push_back({&L->S, &L->v64, &L->v32, &L->d64, &L->d32, &L->bs, &L->bf, n, &L->v16, L->s16, &L->vd16,
                     p2 ? c->mgx_p2_degree : 0});
     H.own.push_back(std::move(L));
     if (!(n % 2 == 0 && n > 2 && ipow(n + 1, D) > (p2 ? c->mg_dense_p2 : c->mg_dense_max))) break;

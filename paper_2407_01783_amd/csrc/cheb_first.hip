@@ -11,11 +11,15 @@ void cheb_first_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, const T
   const int G = lanes_op(c, &S, W, std::is_same<T, float>::value);
   dispatch_w(W, [&](auto Wc) {
     constexpr int WW = decltype(Wc)::value;
-    if (!scaled && S.es > 1 && with_e<WW, std::is_same<T, TM>::value>(S.es, [&](auto Ec) {
+    if (S.es > 1 && (!scaled || !std::is_same<T, TM>::value) && with_e<WW, std::is_same<T, TM>::value>(S.es, [&](auto Ec) {
           constexpr int EE = decltype(Ec)::value;
-          auto kern = accumulate ? k_cheb_first_es<T, WW, 1, EE, TM> : k_cheb_first_es<T, WW, 0, EE, TM>;
-          hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * EE)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), vals,
-                             ms, r, dinv, theta_inv, d1, res, z, c1, c2);
+          auto kern = accumulate ? k_cheb_first_es<T, WW, 1, EE, 0, TM> : k_cheb_first_es<T, WW, 0, EE, 0, TM>;
+          if constexpr (!std::is_same<T, TM>::value)
+            if (scaled)
+              kern = accumulate ? k_cheb_first_es<T, WW, 1, EE, 1, TM> : k_cheb_first_es<T, WW, 0, EE, 1, TM>;
+          const TM* v = scaled ? scaled : vals;
+          hipLaunchKernelGGL(kern, dim3(grid_full(S.nrows * EE)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), v,
+                             v == scaled ? (T)1 : ms, r, dinv, theta_inv, d1, res, z, c1, c2);
         }))
       return;
     with_g<WW>(G, [&](auto Gc) {
@@ -25,8 +29,8 @@ void cheb_first_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, const T
       with_split<GG, WW / GG>(lg, [&](auto SPc) {
         constexpr bool SP = decltype(SPc)::value;
         auto go = [&](auto kern, const TM* v) {
-          hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), v, ms, r, dinv, theta_inv,
-                             d1, res, z, c1, c2, lg);
+          hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), v,
+                             v == scaled ? (T)1 : ms, r, dinv, theta_inv, d1, res, z, c1, c2, lg);
         };
         if (scaled) {
           if (accumulate) go(k_cheb_first<T, WW, 1, GG, 1, TM, SP>, scaled);
@@ -53,10 +57,10 @@ void cheb_first(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* r, 
   cheb_first_impl<T, T>(c, S, vals, (T)1, scaled, W, r, dinv, theta_inv, d1, res, z, c1, c2, accumulate);
 }
 
-void cheb_first_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* r,
-                   const float* dinv, float theta_inv, float* d1, float* res, float* z, float c1, float c2,
-                   int accumulate) {
-  cheb_first_impl<float, _Float16>(c, S, vals, ms, nullptr, W, r, dinv, theta_inv, d1, res, z, c1, c2, accumulate);
+void cheb_first_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, const _Float16* scaled, int W,
+                   const float* r, const float* dinv, float theta_inv, float* d1, float* res, float* z, float c1,
+                   float c2, int accumulate) {
+  cheb_first_impl<float, _Float16>(c, S, vals, ms, scaled, W, r, dinv, theta_inv, d1, res, z, c1, c2, accumulate);
 }
 
 void cheb_first_h(stokes_ctx* c, int W, const float* r, const float* dinv, float theta_inv, float* q1, float* res,

@@ -128,6 +128,7 @@ struct MgLevel {
   DevBuf v64, v32;      // operator values
   DevBuf v16;           // FP32 V-cycles: half-precision values / s16 (empty: none)
   float s16 = 0;
+  DevBuf vd16;          // the same column-scaled (operator x D^-1, unscaled by s16)
   DevBuf d64, d32;      // inverse diagonal
   Bounds bs, bf;        // smoothing interval, full spectrum
 };
@@ -162,6 +163,7 @@ struct MgHier {
     int n;
     const DevBuf* v16 = nullptr;  // half-precision values / s16 (FP32 V-cycles)
     float s16 = 0;
+    const DevBuf* vd16 = nullptr;  // half-precision operator x D^-1 (FP32 V-cycles)
     int nu = 0;  // smoothing degree of this level (0: the context's)
   };
   std::vector<View> lv;

@@ -353,7 +353,8 @@ void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int lv
     }
     if constexpr (std::is_same<T, float>::value) {
       if (v16) {
-        ops::cheb_first_hs(c, S, v16, V.s16, nrb, rin, dinv, (float)k.theta_inv, d0, res, z, (float)k.c1[0],
+        const _Float16* vd16 = V.vd16 && V.vd16->p ? V.vd16->as<_Float16>() : nullptr;
+        ops::cheb_first_hs(c, S, v16, V.s16, vd16, nrb, rin, dinv, (float)k.theta_inv, d0, res, z, (float)k.c1[0],
                            (float)k.c2[0], acc);
         float* da = d0;
         float* db = d1;

@@ -140,9 +140,11 @@ void cheb_step(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* d, T
 // stored values), FP32 vectors: the pressure multigrid levels.
 void spmv_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* x, float* y, float a,
              const float* yin, float b);
-void cheb_first_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* r,
-                   const float* dinv, float theta_inv, float* d1, float* res, float* z, float c1, float c2,
-                   int accumulate);
+// scaled: the half-precision operator x D^-1 (NULL: none), which spares the
+// gathers of dinv where one lane walks a row
+void cheb_first_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, const _Float16* scaled, int W,
+                   const float* r, const float* dinv, float theta_inv, float* d1, float* res, float* z, float c1,
+                   float c2, int accumulate);
 void cheb_step_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* d, float* dn,
                   const float* res_in, float* res_out, float* z, const float* dinv, float c1, float c2);
 // The same with the direction q kept in bfloat16 (W = 3 rows padded to 4).
