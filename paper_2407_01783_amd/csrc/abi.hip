@@ -580,7 +580,7 @@ stokes_status stokes_assemble(const stokes_problem* prob, void* hip_stream, stok
     c->n_p1 = c->mesh.n_q;  // pressure nodes
     c->n_p2 = c->mesh.n_p2;
     c->n_e = c->mesh.n_e;
-    c->red.partials.alloc(size_t(kMaxBlocks) * 2 * kMaxSys * sizeof(double));
+    c->red.partials.alloc(size_t(kMaxBlocks) * (3 * kMaxSys + 2 * kFoldWidth) * sizeof(double));
     c->red.ticket.alloc(64);
     HIP_CHECK(hipMemset(c->red.ticket.p, 0, 64));
     c->red.result.alloc(8 * kMaxSys * sizeof(double));

@@ -117,7 +117,7 @@ void cheb_step_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, 
 
 template <class T>
 void cheb_step(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* d, T* dn, const T* res_in, T* res_out,
-               T* z, const T* dinv, T c1, T c2, const T* rvec, Scalars* sc, int cps, int nsys, int first) {
+               T* z, const T* dinv, T c1, T c2, const T* rvec, Scalars* sc, int cps, int nsys, int rho_mode) {
   // the timed kernel is the plain Chebyshev step (no fused dot) on the velocity block
   const bool timed = rvec == nullptr && prof_begin(c, &S, (const void*)vals, (const void*)avals<T>(c).template as<T>());
   const int G = lanes_op(c, &S, W, std::is_same<T, float>::value);
@@ -131,15 +131,21 @@ void cheb_step(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* d, T
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int lg = rvec ? split_lg_dot(S.nrows, GG, WW / GG) : split_lg(S.nrows, GG, WW / GG);
-      const int nb = rvec && !lg ? grid_for(S.nrows * GG) : grid_rows(S.nrows, GG, lg);
+      int lg = split_lg(S.nrows, GG, WW / GG);
+      const int nb = rvec ? cheb_dot_grid(S.nrows, GG, WW, lg) : grid_rows(S.nrows, GG, lg);
+      double* sums = rvec && rho_mode == RHO_FOLDED ? rho_partials(c) : partials(c);
       with_split<GG, WW / GG>(lg, [&](auto SPc) {
         constexpr bool SP = decltype(SPc)::value;
         auto kern = rvec ? k_cheb_step<T, WW, 1, GG, T, SP> : k_cheb_step<T, WW, 0, GG, T, SP>;
         hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), vals, (T)1, d, dn, res_in,
-                           res_out, z, dinv, c1, c2, rvec, sc, cps, nsys, first, partials(c), lg);
+                           res_out, z, dinv, c1, c2, rvec, sc, cps, nsys, 0, sums, lg);
       });
-      if (rvec) finish_n<WW>(c, nb, FIN_RHO, WW, sc, cps, nsys, first, nullptr);
+      if (!rvec) return;
+      if (rho_mode == RHO_FIRST) finish_n<WW>(c, nb, FIN_RHO, WW, sc, cps, nsys, 1, nullptr);
+      if (rho_mode == RHO_AND_RR)
+        hipLaunchKernelGGL((k_finish_rr_rho<WW>), dim3(1), dim3(kBlock), 0, c->stream, (const double*)rr_partials(c),
+                           grid_for(S.nrows * lanes_rows(c, S.nrows, WW, std::is_same<T, float>::value)),
+                           (const double*)sums, nb, sc, cps, nsys);
     });
   });
   check_launch();

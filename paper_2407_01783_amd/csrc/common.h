@@ -182,10 +182,11 @@ enum { PHASE_VEL = 0, PHASE_PRES = 1, PHASE_ORTH = 2, NUM_PHASES = 3 };
 
 // Per-solver device scalars (one set per Krylov instance).
 struct Scalars {
-  double rho[kMaxSys], rho_old[kMaxSys], alpha[kMaxSys], beta[kMaxSys];
+  double rho[kMaxSys], rho_next[kMaxSys], alpha[kMaxSys], beta[kMaxSys];
   double sigma[kMaxSys], rr[kMaxSys], bb[kMaxSys], tol2[kMaxSys];
   int active[kMaxSys];
   int breakdown;
+  int started;  // folded CG sums: an update has run (rr partials valid)
   int iters;  // of a single-launch CG
 };
 

@@ -50,6 +50,13 @@ void dispatch_dn(int D, int NRB, F&& f) {
 }
 
 inline double* partials(stokes_ctx* c) { return c->red.partials.as<double>(); }
+// the sums of a CG iteration that outlive the kernel after theirs
+inline double* rr_partials(stokes_ctx* c) { return partials(c) + size_t(kMaxBlocks) * 2 * kMaxSys; }
+inline double* sig_partials(stokes_ctx* c) { return rr_partials(c) + size_t(kMaxBlocks) * kMaxSys; }
+inline double* rho_partials(stokes_ctx* c) { return sig_partials(c) + size_t(kMaxBlocks) * kFoldWidth; }
+inline CgSums cg_sums(stokes_ctx* c, const CgPlan& pl) {
+  return {rho_partials(c), rr_partials(c), sig_partials(c), pl.nrho, pl.nrr, pl.nsig};
+}
 
 // Workgroups that cover `rows` rows in one pass of the XCD partition, G lanes
 // per row or 2^lg wavefronts per slice.
@@ -75,18 +82,35 @@ inline int grid_rows(int64_t rows, int G, int lg) {
 //             10.2; 493 k: 22.1 / 20.2 / 26.1, 20.5 / 20.8 / 23.4, 23.0 /
 //             22.3 / 23.7, 15.3 / 14.7 / 16.5; 2.05 M: 56 / 58 / 79,
 //             62 / 65 / 81, 72 / 71 / 73, 47 / 46 / 57
-inline int split_lg(int64_t rows, int G, int wg) {
-  if (G != 1 || !split_width(wg)) return 0;
+inline int split_rows(int64_t rows, int wg) {
   if (rows < (int64_t(1) << 17) && rows * wg < (int64_t(1) << 18)) return 2;
   return wg > 1 && rows < (int64_t(1) << 19) ? 1 : 0;
 }
+inline int split_lg(int64_t rows, int G, int wg) { return G == 1 && split_width(wg) ? split_rows(rows, wg) : 0; }
+
+// Partial sums (workgroups times width) up to which the kernels that use a CG
+// scalar add them up themselves (cg_plan in cg.hip): every wavefront reads all
+// of them.  90,601 rows in 2D, FP32: the update with 2,816 sums to read takes
+// 7.3 us, with 1,424 of them 6.2 us, with none 4.9 us, and a launch that adds
+// them up 3.4 us and the gaps around it.
+constexpr int64_t kFoldMax = 1536;
 
 // The same for a product that ends in a sum over all rows (one partial per
-// workgroup, kMaxBlocks of them).
-inline int split_lg_dot(int64_t rows, int G, int wg) {
-  int lg = split_lg(rows, G, wg);
-  while (lg > 0 && grid_rows(rows, G, lg) > kMaxBlocks) --lg;
+// workgroup, kMaxBlocks of them; fewer wavefronts per slice where that keeps
+// the sums within kFoldMax).
+inline int dot_rows(int64_t rows, int W, int lg) {
+  int lo = lg;
+  while (lo > 0 && grid_rows(rows, 1, lo) * int64_t(W) > kFoldMax) --lo;
+  if ((lo ? grid_rows(rows, 1, lo) : grid_for(rows)) * int64_t(W) <= kFoldMax) return lo;
+  while (lg > 0 && grid_rows(rows, 1, lg) > kMaxBlocks) --lg;
   return lg;
+}
+inline int split_lg_dot(int64_t rows, int G, int wg) { return dot_rows(rows, G * wg, split_lg(rows, G, wg)); }
+
+// Workgroups (and lg) of a Chebyshev step that ends in a sum.
+inline int cheb_dot_grid(int64_t rows, int G, int W, int& lg) {
+  lg = split_lg_dot(rows, G, W / G);
+  return lg ? grid_rows(rows, G, lg) : grid_for(rows * G);
 }
 
 // f(SP): the shared-slice variant of a kernel where lg > 0.

@@ -65,6 +65,9 @@ __device__ __forceinline__ void grid_reduce(double (&v)[NS], double* partials) {
   if (threadIdx.x < NS) partials[(size_t)blockIdx.x * NS + threadIdx.x] = tot[threadIdx.x];
 }
 
+// Widest CG whose scalars are formed where they are used (cg_plan in cg.hip).
+constexpr int kFoldWidth = 4;
+
 enum FinKind { FIN_STORE = 0, FIN_ALPHA = 1, FIN_RR = 2, FIN_RR_RHO = 3, FIN_RHO = 4 };
 
 // Sum the block partials (fixed order) and finish the Krylov scalars:
@@ -119,6 +122,136 @@ __global__ __launch_bounds__(kBlock) void k_finish(const double* __restrict__ pa
     if (sc->active[s] && !(rho > 0)) sc->breakdown = 1;
     sc->rho[s] = rho;
   }
+}
+
+// FIN_RR and FIN_RHO in one launch, each from partials of its own.
+template <int NS>
+__global__ __launch_bounds__(kBlock) void k_finish_rr_rho(const double* __restrict__ prr, int nrr,
+                                                          const double* __restrict__ prho, int nrho, Scalars* sc,
+                                                          int cps, int nsys) {
+  double a[2 * NS];
+#pragma unroll
+  for (int s = 0; s < 2 * NS; ++s) a[s] = 0;
+  for (int b = threadIdx.x; b < nrr; b += blockDim.x) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) a[s] += prr[(size_t)b * NS + s];
+  }
+  for (int b = threadIdx.x; b < nrho; b += blockDim.x) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) a[NS + s] += prho[(size_t)b * NS + s];
+  }
+  __shared__ double tot[2 * NS];
+  block_sum<2 * NS>(a, tot);
+  const int s = threadIdx.x;
+  if (s >= nsys) return;
+  double rr = 0, rho = 0;
+  for (int w = s * cps; w < (s + 1) * cps; ++w) {
+    rr += tot[w];
+    rho += tot[NS + w];
+  }
+  sc->rr[s] = rr;
+  if (sc->active[s] && !(rr > sc->tol2[s])) sc->active[s] = 0;
+  sc->beta[s] = (sc->active[s] && sc->rho[s] != 0) ? rho / sc->rho[s] : 0.0;
+  if (sc->active[s] && !(rho > 0)) sc->breakdown = 1;
+  sc->rho[s] = rho;
+}
+
+// ------------------------------------------- CG scalars where they are used
+//
+// A CG iteration of a mesh of some ten thousand rows is a handful of kernels
+// of 4-10 us, and a launch that only adds up a few hundred partial sums costs
+// 3.4 us and a gap of 1-2.  With at most kFoldMax of them (dispatch.h) every
+// wavefront of the consuming kernel adds them up itself, all in the same
+// order and so to the same bits, and workgroup 0 writes the scalars back at its
+// end.  What a kernel reads and what it writes do not meet: the product reads
+// rho, rr and the started flag and writes rho_next, beta, rr; the update reads
+// rho_next and writes rho, alpha, sigma, started.  active may only fall from 1
+// to 0 by a test that every reader makes itself.  No barrier (rows_split says why).
+struct CgSums {
+  const double *rho = nullptr, *rr = nullptr, *sig = nullptr;  // partials [workgroups][W]
+  int nrho = 0, nrr = 0, nsig = 0;
+};
+
+// totals of the W-slot partials of N sums, in every lane of the wavefront;
+// eight workgroups' worth per lane and sum in flight
+template <int W, int N>
+__device__ __forceinline__ void wave_totals(const double* const (&p)[N], const int (&nb)[N], double (&t)[N][W]) {
+  int top = 0;
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    top = max(top, nb[n]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) t[n][w] = 0;
+  }
+  for (int b0 = threadIdx.x & 63; b0 < top; b0 += 512) {
+    double v[N][8][W];
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int b = b0 + 64 * u;
+#pragma unroll
+        for (int w = 0; w < W; ++w) v[n][u][w] = b < nb[n] ? p[n][(size_t)b * W + w] : 0.0;
+      }
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int w = 0; w < W; ++w) t[n][w] += v[n][u][w];
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o /= 2)
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+      for (int w = 0; w < W; ++w) t[n][w] += __shfl_xor(t[n][w], o);
+}
+
+// sum of the components of system s
+template <int W>
+__device__ __forceinline__ double sys_total(const double (&t)[W], int s, int cps) {
+  double x = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) x += w / cps == s ? t[w] : 0.0;
+  return x;
+}
+
+// rr, rho and what follows from them for system s (the part of FIN_RR and FIN_RHO)
+struct CgBeta {
+  double rr, rho, beta;
+  bool active;
+};
+template <int W>
+__device__ __forceinline__ CgBeta cg_beta(const Scalars* sc, const double (&rr)[W], const double (&rho)[W], int s,
+                                          int cps) {
+  CgBeta o;
+  o.rho = sys_total<W>(rho, s, cps);
+  o.rr = sc->started ? sys_total<W>(rr, s, cps) : sc->rr[s];
+  o.active = sc->active[s] && (!sc->started || o.rr > sc->tol2[s]);
+  o.beta = sc->started && o.active && sc->rho[s] != 0 ? o.rho / sc->rho[s] : 0.0;
+  return o;
+}
+
+// ... written back by one wavefront
+template <int W>
+__device__ __forceinline__ void cg_beta_store(Scalars* sc, const CgSums& cs, int cps, int nsys) {
+  double t[2][W];
+  wave_totals<W, 2>({cs.rr, cs.rho}, {cs.nrr, cs.nrho}, t);
+  const int s = threadIdx.x;
+  if (s >= nsys) return;
+  const CgBeta o = cg_beta<W>(sc, t[0], t[1], s, cps);
+  sc->rr[s] = o.rr;
+  sc->active[s] = o.active ? 1 : 0;
+  sc->beta[s] = o.beta;
+  if (o.active && !(o.rho > 0)) sc->breakdown = 1;
+  sc->rho_next[s] = o.rho;
+}
+
+// the state of a folded CG, brought up to date for the host
+template <int W>
+__global__ void k_cg_state(Scalars* sc, CgSums cs, int cps, int nsys) {
+  cg_beta_store<W>(sc, cs, cps, nsys);
 }
 
 // --------------------------------------------------------- SELL row sums
@@ -610,7 +743,7 @@ __host__ __device__ constexpr bool split_width(int wg) { return wg == 1 || wg ==
 // slot words with vector loads, which costs the velocity step a quarter.)
 template <int G, int WG, typename T, bool LOOP, bool SP, class Prod, class Epi>
 __device__ __forceinline__ void rows_split(int64_t nrows, const int32_t* perm, int lg, Prod&& prod, Epi&& epi) {
-  static_assert(!SP || (G == 1 && split_width(WG)), "one lane per row, narrow rows");
+  static_assert(!SP || (G == 1 && WG <= 3), "one lane per row, narrow rows");
   const int64_t nx = (gridDim.x % 8 == 0) ? gridDim.x / 8 : gridDim.x;
   const int64_t xx = (gridDim.x % 8 == 0) ? blockIdx.x % 8 : 0;
   const int64_t xi = (gridDim.x % 8 == 0) ? blockIdx.x / 8 : blockIdx.x;
@@ -844,21 +977,35 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step_es(int64_t nrows, SellIdx 
 
 // CG direction step with the product folded in:
 //   q = S z (+ extra) + beta q,  p = z + beta p,  sigma = p . q  -> alpha
-template <typename T, int W, int G, bool SP = false>
+// BD = D: vals hold the D x D blocks of the strain operator.  With the blocks
+// the product no longer runs as a kernel of its own that writes S z for this
+// one to read (90,601 rows in 2D, FP32: 10.7 and 4.1 us, and 3.4 for beta's
+// sum; in one, with beta's sum, 12.3 us).
+// FOLD: beta from the partial sums (cs).
+template <typename T, int W, int G, bool SP = false, int BD = 0, bool FOLD = false>
 __global__ __launch_bounds__(kBlock) void k_cg_spmv(int64_t nrows, SellIdx ix,
                                                     const T* __restrict__ vals, const T* __restrict__ z,
                                                     const T* __restrict__ extra, T* __restrict__ q,
-                                                    T* __restrict__ p, Scalars* sc, int cps, int nsys, double* partials, int lg) {
+                                                    T* __restrict__ p, Scalars* sc, int cps, int nsys,
+                                                    double* partials, int lg, CgSums cs) {
   constexpr int WG = W / G;
   const int sub0 = (int)(threadIdx.x % G);
   T beta[WG];
 #pragma unroll
-  for (int w = 0; w < WG; ++w) beta[w] = (T)sc->beta[(sub0 * WG + w) / cps];
+  for (int w = 0; w < WG; ++w)
+    if constexpr (!FOLD) beta[w] = (T)sc->beta[(sub0 * WG + w) / cps];
+  if constexpr (FOLD) {
+    double t[2][W];
+    wave_totals<W, 2>({cs.rr, cs.rho}, {cs.nrr, cs.nrho}, t);
+#pragma unroll
+    for (int w = 0; w < WG; ++w) beta[w] = (T)cg_beta<W>(sc, t[0], t[1], (sub0 * WG + w) / cps, cps).beta;
+  }
   double part[WG];
 #pragma unroll
   for (int w = 0; w < WG; ++w) part[w] = 0;
   auto prod = [&](int64_t row, int sub, RowPart pt, T(&acc)[WG]) {
-    if (ix.sp) sell_row<T, W, G>(ix, vals, z, row, sub, acc, nullptr, pt);
+    if constexpr (BD > 0) sell_row_blk<T, BD, W / (BD > 0 ? BD : 1)>(ix, vals, z, row, acc, pt);
+    else if (ix.sp) sell_row<T, W, G>(ix, vals, z, row, sub, acc, nullptr, pt);
   };
   auto epi = [&](int64_t row, int sub, T(&acc)[WG]) {
 #pragma unroll
@@ -877,21 +1024,37 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(int64_t nrows, SellIdx ix,
   double pf[W];
   expand_parts<W, G>(part, sub0, pf);
   grid_reduce<W>(pf, partials);
+  if constexpr (FOLD) {
+    if (blockIdx.x == 0 && threadIdx.x < 64) cg_beta_store<W>(sc, cs, cps, nsys);
+  }
 }
 
 // PREC: 0 = Chebyshev prologue (d0 = dinv r / theta, z = d0), 1 = Jacobi
 // (z = dinv r, rho = r . z), 2 = none (the preconditioner runs separately).
 // Always: x += alpha p, r -= alpha q, rr = r . r.
-template <typename T, int W, int PREC, int G>
+// FOLD: alpha from the partial sums (cs).
+template <typename T, int W, int PREC, int G, bool FOLD = false>
 __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t nrows, T* __restrict__ x, T* __restrict__ r,
                                                       const T* __restrict__ p, const T* __restrict__ q,
                                                       const T* __restrict__ dinv, T theta_inv, T* __restrict__ d0,
-                                                      T* __restrict__ z, Scalars* sc, int cps, int nsys, double* partials) {
+                                                      T* __restrict__ z, Scalars* sc, int cps, int nsys,
+                                                      double* partials, CgSums cs) {
   constexpr int WG = W / G;
   const int sub0 = (int)(threadIdx.x % G);
   T alpha[WG];
 #pragma unroll
-  for (int w = 0; w < WG; ++w) alpha[w] = (T)sc->alpha[(sub0 * WG + w) / cps];
+  for (int w = 0; w < WG; ++w)
+    if constexpr (!FOLD) alpha[w] = (T)sc->alpha[(sub0 * WG + w) / cps];
+  auto step = [&](const double(&sig)[W], int s, double& sigma) {
+    sigma = sys_total<W>(sig, s, cps);
+    return sc->active[s] && sigma > 0 ? sc->rho_next[s] / sigma : 0.0;
+  };
+  if constexpr (FOLD) {
+    double sig[1][W], sigma;
+    wave_totals<W, 1>({cs.sig}, {cs.nsig}, sig);
+#pragma unroll
+    for (int w = 0; w < WG; ++w) alpha[w] = (T)step(sig[0], (sub0 * WG + w) / cps, sigma);
+  }
   double prr[WG], prz[WG];
 #pragma unroll
   for (int w = 0; w < WG; ++w) prr[w] = prz[w] = 0;
@@ -926,6 +1089,20 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t nrows, T* __restri
     for (int w = 0; w < W; ++w) pf[W + w] = t[w];
   }
   grid_reduce<NS>(pf, partials);
+  if constexpr (FOLD) {
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+      double sig[1][W], sigma;
+      wave_totals<W, 1>({cs.sig}, {cs.nsig}, sig);
+      const int s = threadIdx.x;
+      if (s < nsys) {
+        sc->alpha[s] = step(sig[0], s, sigma);
+        sc->sigma[s] = sigma;
+        if (sc->active[s] && !(sigma > 0)) sc->breakdown = 1;
+        sc->rho[s] = sc->rho_next[s];
+      }
+      if (s == 0) sc->started = 1;
+    }
+  }
 }
 
 // Chebyshev prologue on its own: d0 = dinv r / theta, z = d0.
@@ -1530,12 +1707,14 @@ __device__ __forceinline__ constexpr int sym_index(int a, int b) {
 
 template <typename T, int D, int NRB, int F>
 __device__ __forceinline__ void sell_row_blk_impl(const SellIdx& ix, const SliceRef& rf, const T* __restrict__ vals,
-                                                  const T* __restrict__ x, int64_t row, T (&acc)[D * NRB]) {
+                                                  const T* __restrict__ x, int64_t row, RowPart part,
+                                                  T (&acc)[D * NRB]) {
   constexpr int W = D * NRB, DD = D * (D + 1) / 2;
   const T* __restrict__ vrow = vals + (rf.beg - (row & 63)) * DD + (row & 63);
   constexpr int U = 2;
-  int j = 0;
-  for (; j + U <= rf.width; j += U) {
+  int j, end;
+  part_range<U>(rf.width, part, j, end);
+  for (; j + U <= end; j += U) {
     int32_t c[U];
     T v[U][DD], xv[U][W];
 #pragma unroll
@@ -1558,7 +1737,7 @@ __device__ __forceinline__ void sell_row_blk_impl(const SellIdx& ix, const Slice
           for (int b = 0; b < D; ++b)
             acc[r * D + a] = fma(v[q][sym_index<D>(a, b)], xv[q][r * D + b], acc[r * D + a]);
   }
-  for (; j < rf.width; ++j) {
+  for (; j < end; ++j) {
     const int32_t c = sell_col_f<F>(ix, rf, j);
     T v[DD];
 #pragma unroll
@@ -1575,11 +1754,11 @@ __device__ __forceinline__ void sell_row_blk_impl(const SellIdx& ix, const Slice
 
 template <typename T, int D, int NRB>
 __device__ __forceinline__ void sell_row_blk(const SellIdx& ix, const T* __restrict__ vals, const T* __restrict__ x,
-                                             int64_t row, T (&acc)[D * NRB]) {
+                                             int64_t row, T (&acc)[D * NRB], RowPart part = {}) {
   const SliceRef rf = slice_ref(ix, row);
-  if (rf.af) sell_row_blk_impl<T, D, NRB, 2>(ix, rf, vals, x, row, acc);
-  else if (rf.pk) sell_row_blk_impl<T, D, NRB, 1>(ix, rf, vals, x, row, acc);
-  else sell_row_blk_impl<T, D, NRB, 0>(ix, rf, vals, x, row, acc);
+  if (rf.af) sell_row_blk_impl<T, D, NRB, 2>(ix, rf, vals, x, row, part, acc);
+  else if (rf.pk) sell_row_blk_impl<T, D, NRB, 1>(ix, rf, vals, x, row, part, acc);
+  else sell_row_blk_impl<T, D, NRB, 0>(ix, rf, vals, x, row, part, acc);
 }
 
 // y = a * (A x) + b * yin with the block operator (yin may alias y)
@@ -2259,9 +2438,9 @@ static __global__ void k_scal_init(Scalars* sc, const double* __restrict__ slots
     sc->tol2[s] = rtol2 * bb;
     sc->rr[s] = bb;
     sc->active[s] = (s < nsys && bb > 0) ? 1 : 0;
-    sc->rho[s] = sc->rho_old[s] = sc->alpha[s] = sc->beta[s] = sc->sigma[s] = 0;
+    sc->rho[s] = sc->rho_next[s] = sc->alpha[s] = sc->beta[s] = sc->sigma[s] = 0;
   }
-  if (s == 0) sc->breakdown = 0;
+  if (s == 0) sc->breakdown = sc->started = 0;
 }
 
 // rho from slot sums; beta = rho / rho_prev (0 on the first step)

@@ -121,12 +121,25 @@ template <class T>
 void axpy_sys(stokes_ctx* c, int64_t n, int W, int cps, const double* coef, double scale, const T* v, T* y);
 
 // CG / Chebyshev building blocks (see kernels.h)
+// workgroups of the sums p.q, r.r and r.z of a CG iteration with a Chebyshev
+// preconditioner over the rows of S; fold: no launches of their own for them
+struct CgPlan {
+  int nsig = 0, nrr = 0, nrho = 0;
+  bool fold = false;
+};
+// what cheb_step does with the sum of its last step (rho = r.z)
+enum RhoMode { RHO_FIRST = 1, RHO_AND_RR = 2, RHO_FOLDED = 3 };
 template <class T>
-void cg_spmv(stokes_ctx* c, int64_t nrows, const Sell* S, const T* vals, int W, const T* z, const T* extra, T* q,
-             T* p, Scalars* sc, int cps, int nsys);
+CgPlan cg_plan(stokes_ctx* c, int64_t nrows, const Sell* S, bool blocks, const Sell& pcS, int W);
 template <class T>
-void cg_update(stokes_ctx* c, int64_t nrows, int W, int prec, T* x, T* r, const T* p, const T* q, const T* dinv,
-               T theta_inv, T* d0, T* z, Scalars* sc, int cps, int nsys);
+void cg_state(stokes_ctx* c, const CgPlan& pl, int W, Scalars* sc, int cps, int nsys);
+// blocks: vals are the D x D blocks of the strain operator
+template <class T>
+void cg_spmv(stokes_ctx* c, const CgPlan& pl, int64_t nrows, const Sell* S, const T* vals, bool blocks, int W,
+             const T* z, const T* extra, T* q, T* p, Scalars* sc, int cps, int nsys);
+template <class T>
+void cg_update(stokes_ctx* c, const CgPlan& pl, int64_t nrows, int W, int prec, T* x, T* r, const T* p, const T* q,
+               const T* dinv, T theta_inv, T* d0, T* z, Scalars* sc, int cps, int nsys);
 template <class T>
 void cheb_init(stokes_ctx* c, int64_t nrows, int W, const T* r, const T* dinv, T theta_inv, T* d0, T* z);
 // first Chebyshev step from x0 = 0 with the prologue fused (writes d1, res, z)
@@ -135,7 +148,7 @@ void cheb_first(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* r, 
                 T* res, T* z, T c1, T c2, int accumulate = 0);
 template <class T>
 void cheb_step(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* d, T* dn, const T* res_in, T* res_out,
-               T* z, const T* dinv, T c1, T c2, const T* rvec, Scalars* sc, int cps, int nsys, int first);
+               T* z, const T* dinv, T c1, T c2, const T* rvec, Scalars* sc, int cps, int nsys, int rho_mode);
 // The same operations on half-precision values scaled by 1/ms (S = ms x
 // stored values), FP32 vectors: the pressure multigrid levels.
 void spmv_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, int W, const float* x, float* y, float a,

@@ -199,6 +199,7 @@ class Engine {
     const Sell* S = nullptr;  // fused scalar SELL operator, or
     std::function<void(const T*, T*)> apply;  // composite t = X z
     std::function<void(const T*, T*)> extra;  // added term (augmented Lagrangian)
+    bool blocks = false;      // the values of S are the blocks of the strain operator
     bool small = false;  // the velocity operator alone: may run in one launch
   };
   struct Prec {
@@ -255,6 +256,10 @@ class Engine {
     ops::check_launch();
     const ChebCoef k = cheb_coef(pc.b, pc.degree);
     const T thinv = pc.degree > 1 ? (T)k.theta_inv : (T)1;
+    // the scalars of the iteration: launches of their own, or formed by the
+    // kernels that use them
+    ops::CgPlan plan;
+    if (!pc.apply && pc.degree > 1) plan = ops::cg_plan<T>(c_, nrows, op.apply ? nullptr : op.S, op.blocks, *pc.S, W);
     // z = M^{-1} r with rho = r . z
     auto precond = [&](bool first) {
       if (pc.apply) {
@@ -279,7 +284,8 @@ class Engine {
       for (int j = 1; j < pc.degree; ++j) {
         const bool last = j == pc.degree - 1;
         ops::cheb_step<T>(c_, *pc.S, pc.vals, W, da, db, j == 1 ? r : res, res, z, pc.dinv, (T)k.c1[j - 1],
-                          (T)k.c2[j - 1], last ? r : nullptr, sc, cps, nsys, first ? 1 : 0);
+                          (T)k.c2[j - 1], last ? r : nullptr, sc, cps, nsys,
+                          plan.fold ? ops::RHO_FOLDED : first ? ops::RHO_FIRST : ops::RHO_AND_RR);
         std::swap(da, db);
       }
     };
@@ -290,18 +296,18 @@ class Engine {
     auto body = [&]() {
       if (op.apply) {
         op.apply(z, t);
-        ops::cg_spmv<T>(c_, nrows, nullptr, nullptr, W, z, t, q, p, sc, cps, nsys);
+        ops::cg_spmv<T>(c_, plan, nrows, nullptr, nullptr, false, W, z, t, q, p, sc, cps, nsys);
       } else {
         if (op.extra) op.extra(z, t);
-        ops::cg_spmv<T>(c_, nrows, op.S, opvals, W, z, op.extra ? t : nullptr, q, p, sc, cps, nsys);
+        ops::cg_spmv<T>(c_, plan, nrows, op.S, opvals, op.blocks, W, z, op.extra ? t : nullptr, q, p, sc, cps, nsys);
       }
       if (pc.apply) {
-        ops::cg_update<T>(c_, nrows, W, 2, x, r, p, q, pc.dinv, (T)1, d0, z, sc, cps, nsys);
+        ops::cg_update<T>(c_, plan, nrows, W, 2, x, r, p, q, pc.dinv, (T)1, d0, z, sc, cps, nsys);
         precond(false);
       } else if (pc.degree <= 1) {
-        ops::cg_update<T>(c_, nrows, W, 1, x, r, p, q, pc.dinv, (T)1, d0, z, sc, cps, nsys);
+        ops::cg_update<T>(c_, plan, nrows, W, 1, x, r, p, q, pc.dinv, (T)1, d0, z, sc, cps, nsys);
       } else {
-        ops::cg_update<T>(c_, nrows, W, 0, x, r, p, q, pc.dinv, thinv, d0, z, sc, cps, nsys);
+        ops::cg_update<T>(c_, plan, nrows, W, 0, x, r, p, q, pc.dinv, thinv, d0, z, sc, cps, nsys);
         precond(false);
       }
     };
@@ -319,6 +325,7 @@ class Engine {
       maxit = fixed;  // the check below only looks for breakdown
     }
     for (;;) {
+      if (plan.fold) ops::cg_state<T>(c_, plan, W, sc, cps, nsys);
       sync_scalars(sc_index);
       const Scalars& h = *c_->h_scal;
       check_breakdown(tag, it, nsys);
@@ -391,22 +398,14 @@ class Engine {
       // alpha M + mu (L + D) couples the components; A~_{lambda,3} (the
       // vector-Laplacian block) stays the preconditioner, as in Sec. 3.2
       cps = D_;
-      op.apply = [this](const T* z, T* t) {
-        ops::velop<T>(c_, nrb_, z, t, (T)1, nullptr, (T)0);
-        if (gamma_ > 0) {
-          T* ta = buf("vs_al", nu());
-          al_term(z, ta);
-          ops::axpby<T>(c_, nu(), (T)1, ta, (T)1, t);
-        }
-      };
-    } else {
-      op.S = &c_->sA;
-      if (gamma_ > 0) {
-        op.extra = [this](const T* z, T* t) { al_term(z, t); };
-        cps = D_;
-      }
+      op.blocks = true;
     }
-    st_.inner_u += pcg("vcg", op, A(), pc, c_->n_int, W_, cps, b, x, o_.inner_rtol_u, o_.max_inner, 0, false,
+    op.S = &c_->sA;
+    if (gamma_ > 0) {
+      op.extra = [this](const T* z, T* t) { al_term(z, t); };
+      cps = D_;
+    }
+    st_.inner_u += pcg("vcg", op, c_->strain ? ops::pick<T>(c_->AB64, c_->AB32) : A(), pc, c_->n_int, W_, cps, b, x, o_.inner_rtol_u, o_.max_inner, 0, false,
                        o_.inner_its_u);
   }
 
