@@ -419,7 +419,7 @@ void* stokes_ctx::workspace_host(const std::string& name, size_t bytes) {
   if (e.first && e.second >= bytes) return e.first;
   if (e.first) (void)hipHostFree(e.first);
   e.first = nullptr;
-  if (hipHostMalloc(&e.first, bytes, hipHostMallocDefault) != hipSuccess)
+  if (hipHostMalloc(&e.first, bytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     throw Error(STOKES_ERR_ALLOC, "hipHostMalloc failed");
   e.second = bytes;
   return e.first;

@@ -2249,21 +2249,53 @@ __global__ __launch_bounds__(kBlock) void k_mupdate(int64_t n_int, int64_t n_p1,
 // row mapping and block reduction, so k_mdot_fin gives the same sums as a
 // separate k_mdot pass.  One read of the basis instead of two.  w is read
 // from win (TI, may be w itself) and written in TW.
-// GRAM = 1 (the update with the whole CGS2 coefficients, the new basis
-// column): also ||w||^2 of the stored w as entry nb (chunk nb / 8, slot
+// GRAM = 1: CGS2 in this one update.  The second projection comes from the
+// Gram matrix of the (unnormalized) basis columns C_i, R_ik = C_i . C_k, kept
+// per right-hand side: with the first projection's dots a_i = C_i . w (h) and
+// the squared scales s_i^2 of the columns, its dots are
+//   b_i = C_i . (w - sum_k s_k^2 a_k C_k) = a_i - sum_k R_ik s_k^2 a_k,
+// so w <- w - sum_i s_i^2 (a_i + b_i) C_i gives the CGS2 vector without a
+// second pass over the basis.  Every workgroup forms the coefficients itself
+// (at most 16 products per entry; a launch for them took 2.7-4.6 us of every
+// step), the first one stores a and b for the host in hout, which is host
+// memory (a copy of 12 kB to it took 3.4 us).  The scales come by value with the launch.
+// R: [i][k][r] with strides 64 * 8 and 8.  Also ||w||^2 of the stored w as entry nb (chunk nb / 8, slot
 // nb mod 8), and wf (optional) receives w rounded to TF.  NM: the largest nb
 // (the basis values of a row are held in registers for the dots); launched
 // with 8 up to 8 columns and 16 beyond, up to kFusedMax.
 constexpr int kFusedMax = 16;
+constexpr int kGramLd = 64;
+template <int N>
+struct GramArg {
+  const double* R;
+  double* hout;    // [2][64 * 8]: a, b
+  double sig2[N];  // [column][r]
+};
 template <typename TV, typename TW, int D, int NRB, typename TI = TW, int GRAM = 0, typename TF = TW, int NM = 8>
 __global__ __launch_bounds__(kBlock) void k_mupdate_dot(int64_t n_int, int64_t n_p1, const TV* __restrict__ V,
                                                         int64_t ldv, int nb, const double* __restrict__ h,
                                                         const TI* win, TW* w, double* __restrict__ part,
-                                                        const double* __restrict__ sig2 = nullptr,
-                                                        TF* __restrict__ wf = nullptr) {
+                                                        const double* __restrict__ sig2, TF* __restrict__ wf,
+                                                        GramArg<GRAM ? NM * NRB : 1> ga) {
   constexpr int W = D * NRB, CH = kMdotChunk, NA = NM + GRAM;
   __shared__ double hs[NM * NRB];
-  for (int i = threadIdx.x; i < nb * NRB; i += blockDim.x) hs[i] = -h[i] * (sig2 ? sig2[i] : 1.0);
+  if constexpr (GRAM) {
+    for (int q = threadIdx.x; q < nb * NRB; q += blockDim.x) {
+      const int i = q / NRB, r = q % NRB;
+      double s = 0;
+#pragma unroll
+      for (int k = 0; k < NM; ++k)
+        if (k < nb) s += ga.R[((int64_t)i * kGramLd + k) * 8 + r] * ga.sig2[k * NRB + r] * h[k * NRB + r];
+      const double a = h[q], b = a - s;
+      hs[q] = -(a + b) * ga.sig2[q];
+      if (blockIdx.x == 0) {
+        ga.hout[q] = a;
+        ga.hout[64 * 8 + q] = b;
+      }
+    }
+  } else {
+    for (int i = threadIdx.x; i < nb * NRB; i += blockDim.x) hs[i] = -h[i] * (sig2 ? sig2[i] : 1.0);
+  }
   __syncthreads();
   const int sub = (int)(threadIdx.x % NRB);
   const int64_t nv = n_int * W;
@@ -2350,31 +2382,9 @@ __global__ __launch_bounds__(kBlock) void k_mupdate_dot(int64_t n_int, int64_t n
   }
 }
 
-// CGS2 with the second projection from the Gram matrix of the (unnormalized)
-// basis columns C_i, R_ik = C_i . C_k, kept per right-hand side: with the
-// first projection's dots a_i = C_i . w and the squared scales s_i^2 of the
-// columns, the second projection's dots are
-//   b_i = C_i . (w - sum_k s_k^2 a_k C_k) = a_i - sum_k R_ik s_k^2 a_k,
-// so one update w <- w - sum_i s_i^2 (a_i + b_i) C_i gives the CGS2 vector
-// without a second pass over the basis.  One block; writes b (h2) and a + b
-// (hsum).  R: [i][k][r] with strides 64 * 8 and 8.
-constexpr int kGramLd = 64;
-template <int NRB>
-__global__ __launch_bounds__(kBlock) void k_gram_h2(int nb, const double* __restrict__ R,
-                                                    const double* __restrict__ sig2, const double* __restrict__ h1,
-                                                    double* __restrict__ h2, double* __restrict__ hsum) {
-  for (int q = threadIdx.x; q < nb * NRB; q += blockDim.x) {
-    const int i = q / NRB, r = q % NRB;
-    double s = 0;
-    for (int k = 0; k < nb; ++k) s += R[((int64_t)i * kGramLd + k) * 8 + r] * sig2[k * NRB + r] * h1[k * NRB + r];
-    const double b = h1[i * NRB + r] - s;
-    h2[i * NRB + r] = b;
-    hsum[i * NRB + r] = h1[i * NRB + r] + b;
-  }
-}
-
 // The new column's Gram row from k_mupdate_dot<GRAM = 1>'s partials: entry
-// i < nb is C_i . C_nb, entry nb is ||C_nb||^2 (also written to nrm[r]).
+// i < nb is C_i . C_nb, entry nb is ||C_nb||^2 (also written to nrm[r], which
+// may be host memory).
 // One block per entry.
 template <int NRB>
 __global__ __launch_bounds__(kBlock) void k_gram_fin(int nblk, const double* __restrict__ part, int nb,

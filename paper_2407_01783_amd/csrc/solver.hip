@@ -691,15 +691,12 @@ class Engine {
       sig[r] = active[r] ? 1.0 : 0.0;
       sig2host[r] = sig[r];
     }
-    HIP_CHECK(hipMemcpyAsync(sig2dev, sig2host, R * sizeof(double), hipMemcpyHostToDevice, c_->stream));
     // Gram matrix of the stored columns for the one-update CGS2 (steps with
     // at most kFusedMax columns): column 0 is stored normalized
     const bool gram = c_->gram_cgs2 != 0;
     double* Rg = nullptr;
-    double* hsum = nullptr;
     if (gram) {
       Rg = static_cast<double*>(c_->workspace("gm_R", (size_t)kGramLd * kGramLd * 8 * sizeof(double)));
-      hsum = static_cast<double*>(c_->workspace("gm_hs", 64 * 8 * sizeof(double)));
       double* onesh = static_cast<double*>(c_->workspace_host("gm_R00", 8 * sizeof(double)));
       for (int r = 0; r < 8; ++r) onesh[r] = 1.0;
       HIP_CHECK(hipMemcpyAsync(Rg, onesh, 8 * sizeof(double), hipMemcpyHostToDevice, c_->stream));
@@ -783,31 +780,33 @@ class Engine {
       const bool orth_timed = ops::phase_begin(c_, PHASE_ORTH);
       if (wk) mdot(V, j + 1, (const T*)wk, h1);
       else mdot(V, j + 1, (const TK*)wj, h1);
-      if (gram && j + 1 <= kFusedMax) {
+      const bool one_update = gram && j + 1 <= kFusedMax;
+      if (!one_update)
+        HIP_CHECK(hipMemcpyAsync(sig2dev, sig2host, (j + 1) * R * sizeof(double), hipMemcpyHostToDevice, c_->stream));
+      if (one_update) {
         // CGS2 in one update: the second projection's dots from the Gram
         // matrix, then w <- w - V s^2 (h1 + h2), which also writes the next
         // preconditioner input and the new column's Gram row and norm
         dispatch_dn(D_, nrb_, [&](auto Dc, auto Nc) {
           constexpr int D = decltype(Dc)::value, N = decltype(Nc)::value;
-          hipLaunchKernelGGL((k_gram_h2<N>), dim3(1), dim3(kBlock), 0, c_->stream, j + 1, (const double*)Rg,
-                             (const double*)sig2dev, (const double*)h1, h2, hsum);
-          ops::check_launch();
           auto go = [&](auto NMc) {
             constexpr int NM = decltype(NMc)::value;
+            GramArg<NM * N> ga{Rg, hhost, {}};
+            std::copy(sig2host, sig2host + (j + 1) * N, ga.sig2);
             if (wk)
               hipLaunchKernelGGL((k_mupdate_dot<TK, TK, D, N, T, 1, T, NM>), dim3(nbx), dim3(kBlock), 0, c_->stream,
-                                 c_->n_int, c_->n_p1, (const TK*)V, nc, j + 1, (const double*)hsum, (const T*)wk, wj,
-                                 part, (const double*)sig2dev, vin);
+                                 c_->n_int, c_->n_p1, (const TK*)V, nc, j + 1, (const double*)h1, (const T*)wk, wj,
+                                 part, (const double*)nullptr, vin, ga);
             else
               hipLaunchKernelGGL((k_mupdate_dot<TK, TK, D, N, TK, 1, T, NM>), dim3(nbx), dim3(kBlock), 0, c_->stream,
-                                 c_->n_int, c_->n_p1, (const TK*)V, nc, j + 1, (const double*)hsum, (const TK*)wj, wj,
-                                 part, (const double*)sig2dev, vin);
+                                 c_->n_int, c_->n_p1, (const TK*)V, nc, j + 1, (const double*)h1, (const TK*)wj, wj,
+                                 part, (const double*)nullptr, vin, ga);
           };
           if (j + 1 <= 8) go(std::integral_constant<int, 8>{});
           else go(std::integral_constant<int, kFusedMax>{});
           ops::check_launch();
           hipLaunchKernelGGL((k_gram_fin<N>), dim3(j + 2), dim3(kBlock), 0, c_->stream, nbx, (const double*)part, j + 1,
-                             Rg, nrm);
+                             Rg, hhost + 2 * 64 * 8);
         });
         ops::check_launch();
         // j + 1 basis vectors read once; w_j (or its T copy) read; the next column (and its T copy) written
@@ -821,11 +820,11 @@ class Engine {
             if (wk)
               hipLaunchKernelGGL((k_mupdate_dot<TK, TK, D, N, T, 0, TK, NM>), dim3(nbx), dim3(kBlock), 0, c_->stream,
                                  c_->n_int, c_->n_p1, (const TK*)V, nc, j + 1, (const double*)h1, (const T*)wk, wj,
-                                 part, (const double*)sig2dev, (TK*)nullptr);
+                                 part, (const double*)sig2dev, (TK*)nullptr, GramArg<1>{});
             else
               hipLaunchKernelGGL((k_mupdate_dot<TK, TK, D, N, TK, 0, TK, NM>), dim3(nbx), dim3(kBlock), 0, c_->stream,
                                  c_->n_int, c_->n_p1, (const TK*)V, nc, j + 1, (const double*)h1, (const TK*)wj, wj,
-                                 part, (const double*)sig2dev, (TK*)nullptr);
+                                 part, (const double*)sig2dev, (TK*)nullptr, GramArg<1>{});
           };
           if (j + 1 <= 8) go(std::integral_constant<int, 8>{});
           else go(std::integral_constant<int, kFusedMax>{});
@@ -840,9 +839,10 @@ class Engine {
         mdot(V, j + 1, wj, h2);
       }
       // the second update also leaves the next preconditioner input (in T)
-      if (!(gram && j + 1 <= kFusedMax)) mupdate(V, j + 1, h2, -1.0, wj, nrm, sig2dev, vin);
+      if (!one_update) mupdate(V, j + 1, h2, -1.0, wj, nrm, sig2dev, vin);
       if (orth_timed) ops::phase_end(c_, PHASE_ORTH);
-      HIP_CHECK(hipMemcpyAsync(hhost, hdev, 3 * 64 * 8 * sizeof(double), hipMemcpyDeviceToHost, c_->stream));
+      if (!one_update)
+        HIP_CHECK(hipMemcpyAsync(hhost, hdev, 3 * 64 * 8 * sizeof(double), hipMemcpyDeviceToHost, c_->stream));
       if (queue_ahead && j + 1 < m && est_prev > kQueueAhead * target[0]) {
         HIP_CHECK(hipEventRecord(ev_h, c_->stream));
         precondition(j + 1);
@@ -902,8 +902,6 @@ class Engine {
         // would otherwise grow unnormalized through the later steps)
         if (dropped && any_left) scale_into(s, wj, wj);
         for (int r = 0; r < R; ++r) sig2host[(j + 1) * R + r] = sig[(j + 1) * R + r] * sig[(j + 1) * R + r];
-        HIP_CHECK(hipMemcpyAsync(sig2dev + (j + 1) * R, sig2host + (j + 1) * R, R * sizeof(double),
-                                 hipMemcpyHostToDevice, c_->stream));
       }
     }
     // y = H^{-1} g per right-hand side; x += Z y
