@@ -176,46 +176,65 @@ __global__ __launch_bounds__(kBlock) void k_sweep_out(int64_t n, int64_t ld, int
   }
 }
 
-// y[i][r] = sum_j Cinv[i][j] x[j][r]: one wavefront per row, 16 bytes of the
-// matrix per lane and load, four such loads in flight (the product streams
-// the matrix once and is bound by that; non-temporal, or the up to 100 MB of it
-// push the next level's rows out of the caches: its 36 k-row products right
-// after took 10.3 and 11 us, now 9.3 and 9.3).  ld: row pitch, a multiple of 4.
-template <typename T, int NRB>
+// y[i][r] = sum_j Cinv[i][j] x[j][r]: RW rows per wavefront, 16 bytes of the
+// matrix per lane and load.  The product streams the matrix once (non-temporal,
+// or the up to 100 MB of it push the next level's rows out of the caches: its
+// 36 k-row products right after took 10.3 and 11 us, now 9.3 and 9.3), but
+// every wavefront reads all of x, NRB values per matrix entry, from the L2:
+// with one row per wavefront that is what four to eight right-hand sides wait
+// for (4,913 rows FP32, eight: 97 us, with RW = 4 76 us).  One and three gain
+// nothing from RW = 2 (20.7 and 21.0 us; 3,375 rows 16.7 and 18.6 us).
+// ld: row pitch, a multiple of 4.
+template <typename T, int NRB, int RW>
 __global__ __launch_bounds__(kBlock) void k_dense_mv(int64_t n, int64_t ld, const T* __restrict__ Ci,
                                                      const T* __restrict__ x, T* __restrict__ y) {
   constexpr int V = 16 / sizeof(T), U = NRB <= 4 ? 4 : 1;
   typedef T vec_t __attribute__((ext_vector_type(V)));
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const int64_t row = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * RW;
   if (row >= n) return;  // whole wavefronts exit together
-  const T* __restrict__ ci = Ci + row * ld;
-  double acc[NRB];
+  const T* ci[RW];  // past the last row: the last row again
 #pragma unroll
-  for (int r = 0; r < NRB; ++r) acc[r] = 0;
+  for (int q = 0; q < RW; ++q) ci[q] = Ci + (row + q < n ? row + q : n - 1) * ld;
+  double acc[RW][NRB];
+#pragma unroll
+  for (int q = 0; q < RW; ++q)
+#pragma unroll
+    for (int r = 0; r < NRB; ++r) acc[q][r] = 0;
   auto chunk = [&](auto Uc, int64_t j) {
     constexpr int UU = decltype(Uc)::value;
-    vec_t a[UU];
+    vec_t a[UU][RW];
 #pragma unroll
-    for (int u = 0; u < UU; ++u) a[u] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(ci + j + u * 64 * V));
+    for (int u = 0; u < UU; ++u)
+#pragma unroll
+      for (int q = 0; q < RW; ++q)
+        a[u][q] = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(ci[q] + j + u * 64 * V));
 #pragma unroll
     for (int u = 0; u < UU; ++u)
 #pragma unroll
       for (int v = 0; v < V; ++v)
 #pragma unroll
-        for (int r = 0; r < NRB; ++r) acc[r] += (double)a[u][v] * (double)x[(j + u * 64 * V + v) * NRB + r];
+        for (int r = 0; r < NRB; ++r) {
+          const double xv = (double)x[(j + u * 64 * V + v) * NRB + r];
+#pragma unroll
+          for (int q = 0; q < RW; ++q) acc[q][r] += (double)a[u][q][v] * xv;
+        }
   };
   int64_t j = lane * V;
   for (; j + ((U - 1) * 64 + 1) * V <= n; j += U * 64 * V) chunk(std::integral_constant<int, U>{}, j);
   for (; j + V <= n; j += 64 * V) chunk(std::integral_constant<int, 1>{}, j);
-  for (int64_t q = j; q < n && q < j + V; ++q)  // the columns past the last whole 16 bytes
+  for (int64_t k = j; k < n && k < j + V; ++k)  // the columns past the last whole 16 bytes
 #pragma unroll
-    for (int r = 0; r < NRB; ++r) acc[r] += (double)ci[q] * (double)x[q * NRB + r];
+    for (int q = 0; q < RW; ++q)
 #pragma unroll
-  for (int r = 0; r < NRB; ++r) acc[r] = wave_sum(acc[r]);
-  if (lane == 0)
+      for (int r = 0; r < NRB; ++r) acc[q][r] += (double)ci[q][k] * (double)x[k * NRB + r];
 #pragma unroll
-    for (int r = 0; r < NRB; ++r) y[row * NRB + r] = (T)acc[r];
+  for (int q = 0; q < RW; ++q)
+#pragma unroll
+    for (int r = 0; r < NRB; ++r) {
+      acc[q][r] = wave_sum(acc[q][r]);
+      if (lane == 0 && row + q < n) y[(row + q) * NRB + r] = (T)acc[q][r];
+    }
 }
 
 }  // namespace
@@ -261,8 +280,9 @@ void dense_solve(stokes_ctx* c, const DenseInv& D, int W, const T* x, T* y) {
   const T* Ci = ops::pick<T>(D.i64, D.i32);
   auto go = [&](auto Wc) {
     constexpr int WW = decltype(Wc)::value;
-    hipLaunchKernelGGL((k_dense_mv<T, WW>), dim3((D.n + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0, c->stream,
-                       D.n, D.ld, Ci, x, y);
+    constexpr int RW = WW >= 4 && WW <= 8 ? 4 : 1, rows = RW * kBlock / 64;
+    hipLaunchKernelGGL((k_dense_mv<T, WW, RW>), dim3((D.n + rows - 1) / rows), dim3(kBlock), 0, c->stream, D.n, D.ld,
+                       Ci, x, y);
   };
   switch (W) {
     case 1: go(std::integral_constant<int, 1>{}); break;
