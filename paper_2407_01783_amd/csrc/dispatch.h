@@ -123,8 +123,17 @@ void with_split(int lg, F&& f) {
   f(std::false_type{});
 }
 
-// Lanes per row G of the velocity-row kernels: the largest of 8, 4, 2 not
-// above the request that divides W (the compiled variants).
+// Lanes per row that a request of G gives at width W: the largest of 8, 4, 2
+// not above it that divides W, else 1.  The lanes_* functions below return
+// such numbers, so that a launch and the sums read from its workgroups count
+// the same lanes.
+inline int compiled_lanes(int W, int G) {
+  for (int g : {8, 4, 2})
+    if (G >= g && W % g == 0) return g;
+  return 1;
+}
+
+// f(lanes per row) with a number from compiled_lanes as a constant
 template <int WW, class F>
 void with_g(int G, F&& f) {
   if constexpr (WW % 8 == 0) {
@@ -183,25 +192,25 @@ inline int heuristic_lanes(int W) {
 }
 
 inline int lanes_w(stokes_ctx* c, int W, bool f32) {
-  if (c->force_lanes > 0) return c->force_lanes;
+  if (c->force_lanes > 0) return compiled_lanes(W, c->force_lanes);
   const auto it = c->lanes.find(W * 2 + (f32 ? 1 : 0));
-  return it != c->lanes.end() ? it->second : heuristic_lanes(W);
+  return it != c->lanes.end() ? compiled_lanes(W, it->second) : heuristic_lanes(W);
 }
 
 // B^T rows have their own tuned G (key offset kBtKey)
 constexpr int kBtKey = 1 << 20;
 inline int lanes_bt(stokes_ctx* c, int W, bool f32) {
-  if (c->force_lanes > 0) return c->force_lanes;
+  if (c->force_lanes > 0) return compiled_lanes(W, c->force_lanes);
   const auto it = c->lanes.find(kBtKey + W * 2 + (f32 ? 1 : 0));
-  return it != c->lanes.end() ? it->second : lanes_w(c, W, f32);
+  return it != c->lanes.end() ? compiled_lanes(W, it->second) : lanes_w(c, W, f32);
 }
 
 // the bfloat16-direction Chebyshev kernels too (key offset kQbKey)
 constexpr int kQbKey = 2 << 20;
 inline int lanes_qb(stokes_ctx* c, int W) {
-  if (c->force_lanes > 0) return c->force_lanes;
+  if (c->force_lanes > 0) return compiled_lanes(W, c->force_lanes);
   const auto it = c->lanes.find(kQbKey + W * 2 + 1);
-  return it != c->lanes.end() ? it->second : lanes_w(c, W, true);
+  return it != c->lanes.end() ? compiled_lanes(W, it->second) : lanes_w(c, W, true);
 }
 
 // velocity-row operators use the tuned G; the pressure operators one lane per row
