@@ -1877,6 +1877,36 @@ __global__ __launch_bounds__(kBlock) void k_shift_p(int64_t nrows, const T* src,
   }
 }
 
+// z[row][r] -= mean of slot r of z (from the block partials of its sum, as in
+// k_shift_p), and the sums rvec . z of the result.  sums: an array of its own,
+// since other workgroups still read the partials.
+template <typename T, int NRB>
+__global__ __launch_bounds__(kBlock) void k_shift_dot(int64_t nrows, T* z, const T* __restrict__ rvec,
+                                                      const double* __restrict__ partials, int nparts, double scale,
+                                                      double* __restrict__ sums) {
+  double a[NRB];
+#pragma unroll
+  for (int r = 0; r < NRB; ++r) a[r] = 0;
+  for (int b = threadIdx.x; b < nparts; b += blockDim.x) {
+#pragma unroll
+    for (int r = 0; r < NRB; ++r) a[r] += partials[(size_t)b * NRB + r];
+  }
+  __shared__ double tot[NRB];
+  block_sum<NRB>(a, tot);
+  double part[NRB];
+#pragma unroll
+  for (int r = 0; r < NRB; ++r) part[r] = 0;
+  GRID_STRIDE_ROWS(row, nrows) {
+#pragma unroll
+    for (int r = 0; r < NRB; ++r) {
+      const T v = z[row * NRB + r] - (T)(tot[r] * scale);
+      z[row * NRB + r] = v;
+      part[r] += (double)rvec[row * NRB + r] * (double)v;
+    }
+  }
+  grid_reduce<NRB>(part, sums);
+}
+
 // ------------------------------------------------------- layout transfers
 
 // caller [nrb][D][n_p2] (double) -> internal [n_int][nrb][D] (T), interior only

@@ -108,7 +108,11 @@ std::vector<double> dot_host(stokes_ctx* c, int64_t nrows, int W, const T* x, co
 template <class T>
 void remove_mean(stokes_ctx* c, int nrb, T* x);
 template <class T>
-void remove_mean_into(stokes_ctx* c, int nrb, const T* x, T* y);  // y = x - mean(x) per right-hand side
+void remove_mean_into(stokes_ctx* c, int nrb, const T* x, T* y); // z -= mean per right-hand side, then rho = r . z and beta of a CG whose systems
+// are the right-hand sides (FIN_RHO in kernels.h)
+template <class T>
+void mean_free_rho(stokes_ctx* c, int nrb, const T* r, T* z, Scalars* sc, int first);
+ // y = x - mean(x) per right-hand side
 // x[row][r] -= (m . x_r) / (m . 1) with m = M_Q 1 (zero pressure integral)
 template <class T>
 void normalize_pressure(stokes_ctx* c, int nrb, T* x);

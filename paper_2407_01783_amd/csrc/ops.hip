@@ -273,6 +273,25 @@ void remove_mean_into(stokes_ctx* c, int nrb, const T* x, T* y) {
 }
 
 template <class T>
+void mean_free_rho(stokes_ctx* c, int nrb, const T* r, T* z, Scalars* sc, int first) {
+  const T* ones = std::is_same<T, double>::value ? (const T*)c->ones64.p : (const T*)c->ones32.p;
+  const int nb = grid_for(c->n_p1);
+  dispatch_w(nrb, [&](auto Nc) {
+    constexpr int N = decltype(Nc)::value;
+    hipLaunchKernelGGL((k_dot<T, N>), dim3(nb), dim3(kBlock), 0, c->stream, c->n_p1, (const T*)z, ones,
+                       (const double*)nullptr, (double*)nullptr, partials(c));
+    check_launch();
+    hipLaunchKernelGGL((k_shift_dot<T, N>), dim3(nb), dim3(kBlock), 0, c->stream, c->n_p1, z, r,
+                       (const double*)partials(c), nb, 1.0 / double(c->n_p1), rr_partials(c));
+    check_launch();
+    hipLaunchKernelGGL((k_finish<N>), dim3(1), dim3(kBlock), 0, c->stream, (const double*)rr_partials(c), nb,
+                       (int)FIN_RHO, N, sc, 1, N, first, (double*)nullptr);
+  });
+  check_launch();
+  count_bytes(c, double(c->n_p1) * nrb * sizeof(T) * 4);  // sum pass; z and r read, z written
+}
+
+template <class T>
 void normalize_pressure(stokes_ctx* c, int nrb, T* x) {
   double* res = c->red.result.as<double>() + kMaxSys;
   const T* ones = std::is_same<T, double>::value ? (const T*)c->ones64.p : (const T*)c->ones32.p;
@@ -605,6 +624,7 @@ void adj_dJdmu(stokes_ctx* c, int nrb, const double* u_full, const double* lam, 
   template std::vector<double> dot_host<T>(stokes_ctx*, int64_t, int, const T*, const T*, const double*);           \
   template void remove_mean<T>(stokes_ctx*, int, T*);                                                               \
   template void remove_mean_into<T>(stokes_ctx*, int, const T*, T*);                                                \
+  template void mean_free_rho<T>(stokes_ctx*, int, const T*, T*, Scalars*, int);                                    \
   template void normalize_pressure<T>(stokes_ctx*, int, T*);                                                        \
   template void axpby<T>(stokes_ctx*, int64_t, T, const T*, T, T*);                                                 \
   template void axpy_sys<T>(stokes_ctx*, int64_t, int, int, const double*, double, const T*, T*);                   \

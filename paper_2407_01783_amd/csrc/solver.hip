@@ -209,6 +209,7 @@ class Engine {
     Bounds b;
     int degree;
     std::function<void(const T*, T*)> apply;  // general preconditioner z = M^{-1} r
+    bool mean_free = false;  // apply: on pressures, for an operator that is singular on constants
   };
 
   // Solve op x = b per system to ||r|| <= rtol ||b||; returns iterations.
@@ -264,6 +265,14 @@ class Engine {
     auto precond = [&](bool first) {
       if (pc.apply) {
         pc.apply(r, z);
+        if (pc.mean_free) {
+          // M is nonsingular and M^{-1} largest on constants: the rounding of
+          // the mean of r comes back as a constant in z, which the operator
+          // does not see and which soon outweighs the rest of p.  p . q is
+          // then rounding, in FP32 often negative.
+          ops::mean_free_rho<T>(c_, W, r, z, sc, first ? 1 : 0);
+          return;
+        }
         ops::dot_dev<T>(c_, nrows, W, r, z, nullptr, slots);
         hipLaunchKernelGGL(k_scal_rho, dim3(1), dim3(64), 0, c_->stream, sc, (const double*)slots, cps, nsys,
                            first ? 1 : 0);
@@ -448,6 +457,7 @@ class Engine {
       mg_vcycle<T>(c_, H, nrb_, b, x, 0);
       return;
     }
+    pc.mean_free = true;
     Op op;
     const T* opvals = nullptr;
     if (o_.schur_pc == STOKES_CC_LAPLACE) {
