@@ -728,8 +728,8 @@ stokes_status stokes_apply(stokes_ctx* c, int32_t op, int32_t precision, int32_t
           case 2: ops::Btmul<T>(c, nrb, XP, nullptr, YU, (T)1, nullptr, (T)0); break;
           case 3: ops::spmv<T>(c, c->sQ, ops::pick<T>(c->MQ64, c->MQ32), nrb, XP, YP, (T)1, nullptr, (T)0); break;
           case 4: ops::spmv<T>(c, c->sQ, ops::pick<T>(c->LQ64, c->LQ32), nrb, XP, YP, (T)1, nullptr, (T)0); break;
-          case 6: mg_vcycle<T>(c, c->mgq, nrb, XP, YP, 0); break;
-          case 8: mg_vcycle<T>(c, c->mgx, nrb, XP, YP, 0); break;
+          case 6: mg_vcycle<T>(c, c->mgq, nrb, XP, YP); break;
+          case 8: mg_vcycle<T>(c, c->mgx, nrb, XP, YP); break;
           case 9: vel_vcycle<T>(c, D * nrb, XU, YU, 0); break;
           case 10: vel_cheb_apply<T>(c, nrb, 6, XU, YU); break;
           case 7: ops::spmv<T>(c, c->sX, ops::pick<T>(c->XL64, c->XL32), nrb, XP, YP, (T)1, nullptr, (T)0); break;

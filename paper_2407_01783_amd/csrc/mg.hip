@@ -14,7 +14,8 @@
 //     transpose;
 //   * smoothing: Chebyshev-Jacobi on the upper part of each level's spectrum,
 //     the same polynomial before and after the coarse correction, so the
-//     cycle is symmetric and can precondition CG;
+//     cycle is symmetric and can precondition CG (but for the flexible form
+//     of FP32 cycles, mg_vcycle in ops.h);
 //   * coarsest level: an exact dense inverse where that is cheaper than what
 //     it replaces (build_mg), else a Chebyshev polynomial over its whole
 //     spectrum.
@@ -319,7 +320,7 @@ void build_mg(stokes_ctx* c) {
 }
 
 template <class T>
-void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int lv) {
+void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, bool flexible, int lv) {
   const int nlev = static_cast<int>(H.lv.size());
   if (lv >= nlev) throw Error(STOKES_ERR_STATE, "pressure multigrid hierarchy not built");
   const MgHier::View& V = H.lv[lv];
@@ -353,7 +354,9 @@ void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int lv
     }
     if constexpr (std::is_same<T, float>::value) {
       if (v16) {
-        const _Float16* vd16 = V.vd16 && V.vd16->p ? V.vd16->as<_Float16>() : nullptr;
+        // X D^-1 rounded entry by entry is not D^-1-symmetric (by half
+        // roundings, some 1e-4): only where the caller's method bears that
+        const _Float16* vd16 = flexible && V.vd16 && V.vd16->p ? V.vd16->as<_Float16>() : nullptr;
         ops::cheb_first_hs(c, S, v16, V.s16, vd16, nrb, rin, dinv, (float)k.theta_inv, d0, res, z, (float)k.c1[0],
                            (float)k.c2[0], acc);
         float* da = d0;
@@ -398,7 +401,7 @@ void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int lv
   });
   ops::check_launch();
   ops::count_bytes(c, double(n + ncn) * sizeof(T));  // fine residual read, coarse one written
-  mg_vcycle<T>(c, H, nrb, rc, ec, lv + 1);
+  mg_vcycle<T>(c, H, nrb, rc, ec, flexible, lv + 1);
   dispatch_dn(c->dim, nrb, [&](auto Dc, auto Nc) {
     constexpr int DD = decltype(Dc)::value, N = decltype(Nc)::value;
     hipLaunchKernelGGL((k_prolong_add<T, DD, N>), dim3(ops::grid_for(nr)), dim3(kBlock), 0, c->stream, nf, C.n,
@@ -416,8 +419,8 @@ void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int lv
   }
 }
 
-template void mg_vcycle<double>(stokes_ctx*, const MgHier&, int, const double*, double*, int);
-template void mg_vcycle<float>(stokes_ctx*, const MgHier&, int, const float*, float*, int);
+template void mg_vcycle<double>(stokes_ctx*, const MgHier&, int, const double*, double*, bool, int);
+template void mg_vcycle<float>(stokes_ctx*, const MgHier&, int, const float*, float*, bool, int);
 
 // ======================================================= velocity multigrid
 //

@@ -17,9 +17,13 @@ void build_interleaved(stokes_ctx* c);  // interleaved copies for the bfloat16 C
 // Galerkin hierarchy on B_I Lambda_V^-1 B_I^T + M_Q (levels only; the dense
 // coarsest inverse is added by build_mg)
 void assemble_galerkin(stokes_ctx* c, MgHier& H);
-// e = one multigrid V-cycle of hierarchy H applied to r (pressure layout)
+// e = one multigrid V-cycle of hierarchy H applied to r (pressure layout).
+// flexible: FP32 cycles may use the column-scaled half copy X D^-1 in the
+// first smoothing step.  The cycle is then linear, but symmetric only up to
+// half-precision roundings: for methods that take any linear preconditioner
+// (FGMRES), not for conjugate gradients.
 template <class T>
-void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, int level = 0);
+void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, bool flexible = false, int level = 0);
 // dense inverse of a coarsest level (formed on the device) and y = D x for W
 // interleaved values per row (dense.hip)
 void dense_inverse(stokes_ctx* c, const Sell& S, const double* v64, DenseInv& D);

@@ -445,16 +445,17 @@ class Engine {
   }
 
   // x = X^{-1} b on the mean-free pressures; the preconditioner (fixed
-  // mode: the approximation itself) is one pressure multigrid V-cycle
-  void x_solve(const T* b, T* x) {
+  // mode: the approximation itself) is one pressure multigrid V-cycle.
+  // flexible: of the fixed mode's cycle (mg_vcycle)
+  void x_solve(const T* b, T* x, bool flexible = false) {
     Prec pc{&c_->sQ, ops::pick<T>(c_->XQ64, c_->XQ32), ops::pick<T>(c_->dXQ64, c_->dXQ32), c_->bXQ, 1, {}};
     // the Galerkin hierarchy for the lumped variant (when built), else the
     // V-cycle of eps M_Q + L_Q
     const MgHier& H =
         (o_.schur_pc == STOKES_CC_LUMPED && c_->use_mgx && !c_->mgx.lv.empty()) ? c_->mgx : c_->mgq;
-    pc.apply = [this, &H](const T* r, T* z) { mg_vcycle<T>(c_, H, nrb_, r, z, 0); };
+    pc.apply = [this, &H](const T* r, T* z) { mg_vcycle<T>(c_, H, nrb_, r, z); };
     if (o_.inner_mode == STOKES_INNER_FIXED) {
-      mg_vcycle<T>(c_, H, nrb_, b, x, 0);
+      mg_vcycle<T>(c_, H, nrb_, b, x, flexible);
       return;
     }
     pc.mean_free = true;
@@ -481,7 +482,8 @@ class Engine {
   // to zero up to rounding (B u does for interior u, and the right-hand
   // side's pressure part is made mean-free), and a constant added to z_p
   // changes neither B^T z_p nor K z, only the pressure level that the final
-  // normalization fixes.  Inner CGs on the singular X keep them.
+  // normalization fixes.  Inner CGs on the singular X keep them.  FGMRES also
+  // takes the V-cycle's flexible form.
   void cc_apply(const T* r, T* z, bool mean_free = true) {
     ops::PhaseScope phase(c_, PHASE_PRES);
     mean_free = mean_free || o_.inner_mode != STOKES_INNER_FIXED;
@@ -492,7 +494,7 @@ class Engine {
       ops::remove_mean_into<T>(c_, nrb_, r, rm);
       rin = rm;
     }
-    x_solve(rin, z);
+    x_solve(rin, z, !mean_free);
     cheb_apply("ccq", c_->sQ, ops::pick<T>(c_->MQ64, c_->MQ32), ops::pick<T>(c_->dMQ64, c_->dMQ32), c_->bMQ,
                cc_mq_deg_, nrb_, rin, y);
     ops::axpby<T>(c_, np(), (T)(mu_ * (1.0 + gamma_)), y, (T)alpha_, z);
