@@ -216,7 +216,15 @@ stokes_status stokes_host_pattern(const stokes_problem* prob, int32_t which, int
 
 /* Build the mesh, assemble every operator on the GPU (Sec. 2.2, 3.2, 4.1:
  * M_V, L_V, B, M_Q, L_Q, Lambda_V), estimate the Chebyshev bounds and return a
- * context bound to hip_stream (NULL = default stream) and the current device. */
+ * context bound to hip_stream (NULL = default stream) and the current device.
+ *
+ * Multigrid hierarchies solve a coarsest level of at most 9,000 rows by its
+ * dense inverse.  It is formed when a solve first uses the hierarchy in a
+ * precision and kept: 4 (FP32) or 8 bytes per entry, at most 324 or 648 MB,
+ * and as much again as 8 bytes per entry while it is formed.  Where that takes
+ * more than half of the free device memory, or than STOKES_DENSE_MB (an
+ * environment variable read here), that level is solved by a polynomial
+ * instead, with the same answers in more iterations. */
 stokes_status stokes_assemble(const stokes_problem* prob, void* hip_stream, stokes_ctx** out);
 
 /* Method 1 (Sec. 2.3): flexible CG on the pressure Schur complement

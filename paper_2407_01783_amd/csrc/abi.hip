@@ -558,6 +558,7 @@ stokes_status stokes_assemble(const stokes_problem* prob, void* hip_stream, stok
     if (const char* e = std::getenv("STOKES_VEL_AF")) c->vel_af = std::atoi(e) != 0;
     if (const char* e = std::getenv("STOKES_CHEB_DEFER")) c->cheb_defer = std::atoi(e) != 0;
     if (const char* e = std::getenv("STOKES_GRAM")) c->gram_cgs2 = std::atoi(e) != 0;
+    if (const char* e = std::getenv("STOKES_DENSE_MB"); e && *e) c->dense_bytes = std::atoll(e) < 0 ? -1 : std::atoll(e) << 20;
     if (const char* e = std::getenv("STOKES_LANES")) c->force_lanes = std::max(0, std::atoi(e));
     if (const char* e = std::getenv("STOKES_ZBLOCK")) c->zblock = std::max(0, std::atoi(e));
     if (const char* e = std::getenv("STOKES_VEL_PAIR")) c->vel_pair = std::max(0, std::min(2, std::atoi(e)));
@@ -728,9 +729,18 @@ stokes_status stokes_apply(stokes_ctx* c, int32_t op, int32_t precision, int32_t
           case 2: ops::Btmul<T>(c, nrb, XP, nullptr, YU, (T)1, nullptr, (T)0); break;
           case 3: ops::spmv<T>(c, c->sQ, ops::pick<T>(c->MQ64, c->MQ32), nrb, XP, YP, (T)1, nullptr, (T)0); break;
           case 4: ops::spmv<T>(c, c->sQ, ops::pick<T>(c->LQ64, c->LQ32), nrb, XP, YP, (T)1, nullptr, (T)0); break;
-          case 6: mg_vcycle<T>(c, c->mgq, nrb, XP, YP); break;
-          case 8: mg_vcycle<T>(c, c->mgx, nrb, XP, YP); break;
-          case 9: vel_vcycle<T>(c, D * nrb, XU, YU, 0); break;
+          case 6:
+            mg_ready<T>(c, c->mgq);
+            mg_vcycle<T>(c, c->mgq, nrb, XP, YP);
+            break;
+          case 8:
+            mg_ready<T>(c, c->mgx);
+            mg_vcycle<T>(c, c->mgx, nrb, XP, YP);
+            break;
+          case 9:
+            vmg_ready<T>(c);
+            vel_vcycle<T>(c, D * nrb, XU, YU, 0);
+            break;
           case 10: vel_cheb_apply<T>(c, nrb, 6, XU, YU); break;
           case 7: ops::spmv<T>(c, c->sX, ops::pick<T>(c->XL64, c->XL32), nrb, XP, YP, (T)1, nullptr, (T)0); break;
           default:

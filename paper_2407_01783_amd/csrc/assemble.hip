@@ -1758,7 +1758,6 @@ void download_csr(stokes_ctx* c, const DevCsr& P, const DevBuf& v, HostCsr& h, s
 void assemble_galerkin(stokes_ctx* c, MgHier& H) {
   H.lv.clear();
   H.own.clear();
-  H.dense.n = 0;
   const int D = c->dim;
   // level 0: B_I Lambda_V^-1 B_I^T + M_Q on the union of the two patterns
   HostCsr X, Q, A;

@@ -147,10 +147,20 @@ struct VmgLevel {
   DevBuf pv64, pv32, rv64, rv32;
 };
 
-// Dense inverse of a coarsest multigrid operator: rows of ld values (pads 0).
+// Dense inverse of a coarsest multigrid operator: rows of ld values (pads 0),
+// formed in a precision when a solve first asks for it (dense_ready), since
+// most programs use one precision and one hierarchy.
 struct DenseInv {
-  int64_t n = 0, ld = 0;  // n = 0: none
+  int64_t n = 0, ld = 0;  // n = 0: the level is not solved densely
   DevBuf i64, i32;
+  bool tried64 = false, tried32 = false;  // asked for: formed, or without the memory for it
+  void reset(int64_t rows) {
+    n = rows;
+    ld = (rows + 3) / 4 * 4;
+    i64.release();
+    i32.release();
+    tried64 = tried32 = false;
+  }
 };
 
 // A multigrid hierarchy on the nested Kuhn meshes n, n/2, ...  Level views
@@ -168,7 +178,7 @@ struct MgHier {
   };
   std::vector<View> lv;
   std::vector<std::unique_ptr<MgLevel>> own;
-  DenseInv dense;  // of the coarsest level (n = 0: a polynomial over its whole spectrum)
+  DenseInv dense;  // of the coarsest level (without one: a polynomial over its whole spectrum)
 };
 
 // GPU time of one solver phase, from pairs of HIP events recorded on the
@@ -275,6 +285,10 @@ struct stokes_ctx {
   // mg_dense_last, where it cannot (an odd cell count): the polynomial over
   // the whole spectrum is 24 launches, 100-140 / 150 us, and less exact.
   int64_t mg_dense_max = 5000, mg_dense_p2 = 1500, mg_dense_last = 9000;
+  // Bytes that forming one inverse may take, itself and its working copy
+  // (< 0: half of the device memory that is free at the time).  Beyond that the
+  // level is solved by the polynomial.
+  int64_t dense_bytes = -1;
   double mg_smooth_ratio = 10.0;
   int use_mgx = 1;                      // lumped CC: precondition with mgx (0: mgq)
   // P3/P2: build the Galerkin hierarchy too (0: only the eps M_Q + L_Q one),

@@ -164,15 +164,15 @@ __global__ __launch_bounds__(kBlock) void k_sweep_update(int64_t N, int64_t k, d
     for (int j = 0; j < 4; ++j) A[(I * kTile + 4 * ty + i) * N + J * kTile + 4 * tx + j] -= acc[i][j];
 }
 
-// The inverse in full (rows of ld values, pads 0), in both precisions
+// The inverse in full (rows of ld values, pads 0)
+template <typename T>
 __global__ __launch_bounds__(kBlock) void k_sweep_out(int64_t n, int64_t ld, int64_t N, const double* __restrict__ A,
-                                                      double* __restrict__ i64, float* __restrict__ i32) {
+                                                      T* __restrict__ inv) {
   const int64_t i = blockIdx.x;
   for (int64_t j = threadIdx.x; j < ld; j += blockDim.x) {
     double v = 0;
     if (j < n) v = -(i >= j ? A[i * N + j] : A[j * N + i]);
-    i64[i * ld + j] = v;
-    i32[i * ld + j] = (float)v;
+    inv[i * ld + j] = (T)v;
   }
 }
 
@@ -239,18 +239,18 @@ __global__ __launch_bounds__(kBlock) void k_dense_mv(int64_t n, int64_t ld, cons
 
 }  // namespace
 
-void dense_inverse(stokes_ctx* c, const Sell& S, const double* v64, DenseInv& D) {
+namespace {
+
+template <class T>
+void form_inverse(stokes_ctx* c, const Sell& S, const double* v64, const DenseInv& D, DevBuf& out) {
   const int64_t n = S.nrows, nt = (n + kTile - 1) / kTile, N = nt * kTile;
-  D.n = 0;
-  D.ld = (n + 3) / 4 * 4;
-  DevBuf A, P, T, Q, bad;
+  DevBuf A, P, T_, Q, bad;
   A.alloc(N * N * sizeof(double));
   P.alloc(kTile * kTile * sizeof(double));
-  T.alloc(N * kTile * sizeof(double));
+  T_.alloc(N * kTile * sizeof(double));
   Q.alloc(N * kTile * sizeof(double));
   bad.alloc(sizeof(int));
-  D.i64.alloc(n * D.ld * sizeof(double));
-  D.i32.alloc(n * D.ld * sizeof(float));
+  out.alloc(n * D.ld * sizeof(T));
   HIP_CHECK(hipMemsetAsync(A.p, 0, N * N * sizeof(double), c->stream));
   HIP_CHECK(hipMemsetAsync(bad.p, 0, sizeof(int), c->stream));
   hipLaunchKernelGGL(k_sell_to_dense, dim3(ops::grid_for(n)), dim3(kBlock), 0, c->stream, n,
@@ -261,19 +261,57 @@ void dense_inverse(stokes_ctx* c, const Sell& S, const double* v64, DenseInv& D)
     hipLaunchKernelGGL(k_sweep_pivot, dim3(1), dim3(kBlock), 0, c->stream, N, k, A.as<const double>(), P.as<double>(),
                        bad.as<int>());
     hipLaunchKernelGGL(k_sweep_panel, dim3(nt), dim3(kBlock), 0, c->stream, N, k, A.as<double>(), P.as<const double>(),
-                       T.as<double>(), Q.as<double>());
+                       T_.as<double>(), Q.as<double>());
     hipLaunchKernelGGL(k_sweep_update, dim3(nt, nt), dim3(kBlock), 0, c->stream, N, k, A.as<double>(),
-                       T.as<const double>(), Q.as<const double>());
+                       T_.as<const double>(), Q.as<const double>());
   }
-  hipLaunchKernelGGL(k_sweep_out, dim3(n), dim3(kBlock), 0, c->stream, n, D.ld, N, A.as<const double>(),
-                     D.i64.as<double>(), D.i32.as<float>());
+  hipLaunchKernelGGL(k_sweep_out<T>, dim3(n), dim3(kBlock), 0, c->stream, n, D.ld, N, A.as<const double>(),
+                     out.as<T>());
   ops::check_launch();
   int hbad = 0;
   HIP_CHECK(hipMemcpyAsync(&hbad, bad.p, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   HIP_CHECK(hipStreamSynchronize(c->stream));
-  if (hbad) throw Error(STOKES_ERR_BREAKDOWN, "coarsest multigrid operator is not positive definite");
-  D.n = n;
+  if (hbad) {
+    out.release();
+    throw Error(STOKES_ERR_BREAKDOWN, "coarsest multigrid operator is not positive definite");
+  }
 }
+
+}  // namespace
+
+template <class T>
+void dense_ready(stokes_ctx* c, const Sell& S, const double* v64, DenseInv& D) {
+  constexpr bool f32 = std::is_same<T, float>::value;
+  bool& tried = f32 ? D.tried32 : D.tried64;
+  if (D.n == 0 || tried) return;
+  const size_t need = (size_t(D.n + kTile) * (D.n + kTile) + size_t(2 * kTile) * (D.n + kTile)) * sizeof(double) +
+                      size_t(D.n) * D.ld * sizeof(T);
+  size_t cap = size_t(c->dense_bytes);
+  if (c->dense_bytes < 0) {
+    size_t free_b = 0, total = 0;
+    HIP_CHECK(hipMemGetInfo(&free_b, &total));
+    cap = free_b / 2;
+  }
+  DevBuf& out = f32 ? D.i32 : D.i64;
+  if (need <= cap) {
+    try {
+      form_inverse<T>(c, S, v64, D, out);
+    } catch (const Error& e) {
+      out.release();
+      if (e.code != STOKES_ERR_ALLOC) throw;
+    }
+  }
+  tried = true;
+}
+template void dense_ready<float>(stokes_ctx*, const Sell&, const double*, DenseInv&);
+template void dense_ready<double>(stokes_ctx*, const Sell&, const double*, DenseInv&);
+
+template <class T>
+bool dense_has(const DenseInv& D) {
+  return D.n > 0 && ops::pick<T>(D.i64, D.i32) != nullptr;
+}
+template bool dense_has<float>(const DenseInv&);
+template bool dense_has<double>(const DenseInv&);
 
 template <class T>
 void dense_solve(stokes_ctx* c, const DenseInv& D, int W, const T* x, T* y) {

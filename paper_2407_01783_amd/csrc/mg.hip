@@ -192,12 +192,16 @@ void dispatch_w_mg(int W, F&& f) {
 
 }  // namespace
 
-// Dense inverse of the coarsest level when it is small enough.
-static void dense_coarsest(stokes_ctx* c, MgHier& H) {
-  const MgHier::View& V = H.lv.back();
-  H.dense.n = 0;
-  if (V.S->nrows <= c->mg_dense_last) dense_inverse(c, *V.S, V.v64->as<const double>(), H.dense);
+// The coarsest level is solved by its dense inverse when it is small enough.
+static int64_t dense_rows(stokes_ctx* c, int64_t nrows) { return nrows <= c->mg_dense_last ? nrows : 0; }
+
+template <class T>
+void mg_ready(stokes_ctx* c, MgHier& H) {
+  if (H.lv.empty()) return;
+  dense_ready<T>(c, *H.lv.back().S, H.lv.back().v64->as<const double>(), H.dense);
 }
+template void mg_ready<double>(stokes_ctx*, MgHier&);
+template void mg_ready<float>(stokes_ctx*, MgHier&);
 
 // Entry-split lanes per level (Sell::es).  The coarse levels have a few
 // thousand rows of a two-ring stencil, where one lane per row leaves the chip
@@ -300,7 +304,7 @@ void build_mg(stokes_ctx* c) {
     H.lv.push_back({&L->S, &L->v64, &L->v32, &L->d64, &L->d32, &L->bs, &L->bf, n});
     H.own.push_back(std::move(L));
   }
-  dense_coarsest(c, H);
+  H.dense.reset(dense_rows(c, H.lv.back().S->nrows));
   // The Galerkin hierarchy of B_I Lambda_V^-1 B_I^T + M_Q.  On the P2
   // pressure of a P3/P2 pair that operator is close to the P2 mass matrix,
   // whose low-energy modes include non-smooth ones (vertex and edge values
@@ -310,10 +314,10 @@ void build_mg(stokes_ctx* c) {
   // stays symmetric positive definite and is the better preconditioner.
   c->mgx.lv.clear();
   c->mgx.own.clear();
-  c->mgx.dense.n = 0;
+  c->mgx.dense.reset(0);
   if (fm.order != 3 || c->mgx_p3) {
     assemble_galerkin(c, c->mgx);
-    dense_coarsest(c, c->mgx);
+    c->mgx.dense.reset(dense_rows(c, c->mgx.lv.back().S->nrows));
   }
   tune_levels(c, c->mgq);
   tune_levels(c, c->mgx);
@@ -378,7 +382,7 @@ void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, bool f
     }
   };
   if (lv == nlev - 1) {  // coarsest: dense inverse, or a polynomial over the whole spectrum
-    if (H.dense.n == nr) {
+    if (dense_has<T>(H.dense)) {
       dense_solve<T>(c, H.dense, nrb, r, e);
     } else {
       cheb(bf, c->mg_coarse_degree, r, e, 0);
@@ -435,11 +439,12 @@ template void mg_vcycle<float>(stokes_ctx*, const MgHier&, int, const float*, fl
 //     transpose, coarse Dirichlet nodes dropped;
 //   * Chebyshev-Jacobi smoothing on the upper spectrum, the same polynomial
 //     before and after the correction, so the cycle is symmetric positive
-//     definite; the coarsest level (<= mg_dense_max rows) is solved densely.
+//     definite; a coarsest level of at most mg_dense_last rows is solved densely.
 
 void build_vmg(stokes_ctx* c) {
+  c->vmg_built = false;
   c->vmg.clear();
-  c->vmg_dense.n = 0;
+  c->vmg_dense.reset(0);
   const HostMesh& fm = c->mesh;
   const int D = fm.dim;
   int nf = fm.n, stride = 1;
@@ -493,14 +498,20 @@ void build_vmg(stokes_ctx* c) {
     c->vmg.push_back(std::move(L));
     nf = nc;
   }
-  // coarsest level: dense inverse when small
-  const Sell& Sc = c->vmg.empty() ? c->sA : c->vmg.back()->S;
-  const DevBuf& vc = c->vmg.empty() ? c->A64 : c->vmg.back()->v64;
-  if (Sc.nrows <= c->mg_dense_last) dense_inverse(c, Sc, vc.as<const double>(), c->vmg_dense);
+  c->vmg_dense.reset(dense_rows(c, c->vmg.empty() ? c->sA.nrows : c->vmg.back()->nrows));
   HIP_CHECK(hipStreamSynchronize(c->stream));
   c->vmg_mu = c->prob.mu;
   c->vmg_built = true;
 }
+
+template <class T>
+void vmg_ready(stokes_ctx* c) {
+  const Sell& S = c->vmg.empty() ? c->sA : c->vmg.back()->S;
+  const DevBuf& v = c->vmg.empty() ? c->A64 : c->vmg.back()->v64;
+  dense_ready<T>(c, S, v.as<const double>(), c->vmg_dense);
+}
+template void vmg_ready<double>(stokes_ctx*);
+template void vmg_ready<float>(stokes_ctx*);
 
 template <class T>
 void vel_vcycle(stokes_ctx* c, int W, const T* r, T* e, int lv) {
@@ -529,7 +540,7 @@ void vel_vcycle(stokes_ctx* c, int W, const T* r, T* e, int lv) {
     }
   };
   if (lv == nlev - 1) {  // coarsest
-    if (c->vmg_dense.n == nr) {
+    if (dense_has<T>(c->vmg_dense)) {
       dense_solve<T>(c, c->vmg_dense, W, r, e);
     } else {
       cheb(bf, c->mg_coarse_degree, r, e, 0);

@@ -23,16 +23,26 @@ void assemble_galerkin(stokes_ctx* c, MgHier& H);
 // half-precision roundings: for methods that take any linear preconditioner
 // (FGMRES), not for conjugate gradients.
 template <class T>
+void mg_ready(stokes_ctx* c, MgHier& H);  // before the first cycle in T (dense_ready)
+template <class T>
 void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, bool flexible = false, int level = 0);
-// dense inverse of a coarsest level (formed on the device) and y = D x for W
-// interleaved values per row (dense.hip)
-void dense_inverse(stokes_ctx* c, const Sell& S, const double* v64, DenseInv& D);
+// Dense inverse of a coarsest level (dense.hip).  dense_ready: forms it in T
+// unless that has been tried (allocates and synchronises: outside captures,
+// before the first V-cycle in T); without the memory for it dense_has stays
+// false and the level is solved by a polynomial.  dense_solve: y = D x for W
+// interleaved values per row.
+template <class T>
+void dense_ready(stokes_ctx* c, const Sell& S, const double* v64, DenseInv& D);
+template <class T>
+bool dense_has(const DenseInv& D);
 template <class T>
 void dense_solve(stokes_ctx* c, const DenseInv& D, int W, const T* x, T* y);
 // velocity multigrid: coarse level assembly, hierarchy build, one V-cycle of
 // alpha M + mu L applied to W = dim x nrhs interleaved components
 void assemble_p2_level(stokes_ctx* c, const HostMesh& m, VmgLevel& L);
 void build_vmg(stokes_ctx* c);
+template <class T>
+void vmg_ready(stokes_ctx* c);  // before the first cycle in T (dense_ready)
 template <class T>
 void vel_vcycle(stokes_ctx* c, int W, const T* r, T* e, int level = 0);
 void estimate_bounds(stokes_ctx* c);

@@ -394,6 +394,7 @@ class Engine {
     ops::PhaseScope phase(c_, PHASE_VEL);
     Prec pc{&c_->sA, A(), dA(), c_->bA, std::max(1, o_.cheb_degree), {}};
     const bool mg = o_.vel_pc == STOKES_VEL_MG;
+    if (mg) vmg_ready<T>(c_);
     if (mg) pc.apply = [this](const T* r, T* z) { vel_vcycle<T>(c_, W_, r, z, 0); };
     if (o_.inner_mode == STOKES_INNER_FIXED) {
       if (mg) vel_vcycle<T>(c_, W_, b, x, 0);
@@ -451,8 +452,9 @@ class Engine {
     Prec pc{&c_->sQ, ops::pick<T>(c_->XQ64, c_->XQ32), ops::pick<T>(c_->dXQ64, c_->dXQ32), c_->bXQ, 1, {}};
     // the Galerkin hierarchy for the lumped variant (when built), else the
     // V-cycle of eps M_Q + L_Q
-    const MgHier& H =
+    MgHier& H =
         (o_.schur_pc == STOKES_CC_LUMPED && c_->use_mgx && !c_->mgx.lv.empty()) ? c_->mgx : c_->mgq;
+    mg_ready<T>(c_, H);
     pc.apply = [this, &H](const T* r, T* z) { mg_vcycle<T>(c_, H, nrb_, r, z); };
     if (o_.inner_mode == STOKES_INNER_FIXED) {
       mg_vcycle<T>(c_, H, nrb_, b, x, flexible);
