@@ -2284,7 +2284,7 @@ __global__ __launch_bounds__(kBlock) void k_mupdate(int64_t n_int, int64_t n_p1,
 // so w <- w - sum_i s_i^2 (a_i + b_i) C_i gives the CGS2 vector without a
 // second pass over the basis.  Every workgroup forms the coefficients itself
 // (at most 16 products per entry; a launch for them took 2.7-4.6 us of every
-// step), the first one stores a and b for the host in hout, which is host
+// step, forming them here 1-5), the first one stores a and b for the host in hout, which is host
 // memory (a copy of 12 kB to it took 3.4 us).  The scales come by value with the launch.
 // R: [i][k][r] with strides 64 * 8 and 8.  Also ||w||^2 of the stored w as entry nb (chunk nb / 8, slot
 // nb mod 8), and wf (optional) receives w rounded to TF.  NM: the largest nb
@@ -2298,8 +2298,18 @@ struct GramArg {
   double* hout;    // [2][64 * 8]: a, b
   double sig2[N];  // [column][r]
 };
+// Registers: with 16 FP64 columns of several right-hand sides the coefficients'
+// code took the 3D kernel to 257 of them, one wavefront per SIMD instead of two.
+// FP64 basis, 36 cells in 3D, up to 16 columns, two / four / eight right-hand
+// sides: 46 / 83 / 159 us and a launch and two copies more (11 us) when the
+// coefficients had a launch of their own; formed here 91 / 133 / 205 us; with
+// the registers bounded and the loads in flight together 48 / 85 / 171 us.
+template <typename TV, int NRB, int NM>
+constexpr int mupdate_waves() {
+  return NM > 8 && sizeof(TV) == 8 && NRB > 1 ? 2 : 1;
+}
 template <typename TV, typename TW, int D, int NRB, typename TI = TW, int GRAM = 0, typename TF = TW, int NM = 8>
-__global__ __launch_bounds__(kBlock) void k_mupdate_dot(int64_t n_int, int64_t n_p1, const TV* __restrict__ V,
+__global__ __launch_bounds__(kBlock, (mupdate_waves<TV, NRB, NM>())) void k_mupdate_dot(int64_t n_int, int64_t n_p1, const TV* __restrict__ V,
                                                         int64_t ldv, int nb, const double* __restrict__ h,
                                                         const TI* win, TW* w, double* __restrict__ part,
                                                         const double* __restrict__ sig2, TF* __restrict__ wf,
@@ -2309,10 +2319,19 @@ __global__ __launch_bounds__(kBlock) void k_mupdate_dot(int64_t n_int, int64_t n
   if constexpr (GRAM) {
     for (int q = threadIdx.x; q < nb * NRB; q += blockDim.x) {
       const int i = q / NRB, r = q % NRB;
+      // every load first (past column nb - 1: that column again, scale 0): as
+      // loads under k < nb they were NM round trips to the L2 in a row (2D, 128
+      // cells, eight right-hand sides, FP64, 16 columns 47.9 -> 35.6 us)
+      double g[NM], hk[NM];
+#pragma unroll
+      for (int k = 0; k < NM; ++k) {
+        const int kk = min(k, nb - 1);
+        g[k] = ga.R[((int64_t)i * kGramLd + kk) * 8 + r];
+        hk[k] = h[kk * NRB + r];
+      }
       double s = 0;
 #pragma unroll
-      for (int k = 0; k < NM; ++k)
-        if (k < nb) s += ga.R[((int64_t)i * kGramLd + k) * 8 + r] * ga.sig2[k * NRB + r] * h[k * NRB + r];
+      for (int k = 0; k < NM; ++k) s += g[k] * ga.sig2[k * NRB + r] * hk[k];
       const double a = h[q], b = a - s;
       hs[q] = -(a + b) * ga.sig2[q];
       if (blockIdx.x == 0) {
