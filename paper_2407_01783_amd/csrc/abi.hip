@@ -730,11 +730,11 @@ stokes_status stokes_apply(stokes_ctx* c, int32_t op, int32_t precision, int32_t
           case 3: ops::spmv<T>(c, c->sQ, ops::pick<T>(c->MQ64, c->MQ32), nrb, XP, YP, (T)1, nullptr, (T)0); break;
           case 4: ops::spmv<T>(c, c->sQ, ops::pick<T>(c->LQ64, c->LQ32), nrb, XP, YP, (T)1, nullptr, (T)0); break;
           case 6:
-            mg_ready<T>(c, c->mgq);
+            mg_ready<T>(c, c->mgq, nrb);
             mg_vcycle<T>(c, c->mgq, nrb, XP, YP);
             break;
           case 8:
-            mg_ready<T>(c, c->mgx);
+            mg_ready<T>(c, c->mgx, nrb);
             mg_vcycle<T>(c, c->mgx, nrb, XP, YP);
             break;
           case 9:

@@ -1793,7 +1793,7 @@ void assemble_galerkin(stokes_ctx* c, MgHier& H) {
     H.lv.push_back({&L->S, &L->v64, &L->v32, &L->d64, &L->d32, &L->bs, &L->bf, n, &L->v16, L->s16, &L->vd16,
                     p2 ? c->mgx_p2_degree : 0});
     H.own.push_back(std::move(L));
-    if (!(n % 2 == 0 && n > 2 && ipow(n + 1, D) > (p2 ? c->mg_dense_p2 : c->mg_dense_max))) break;
+    if (!(n % 2 == 0 && n > 2 && ipow(n + 1, D) > c->mg_dense_low)) break;
     HostCsr Ac;
     std::vector<double> acv;
     galerkin_p1(D, n, n / 2, A, av, Ac, acv);

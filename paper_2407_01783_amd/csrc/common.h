@@ -178,7 +178,11 @@ struct MgHier {
   };
   std::vector<View> lv;
   std::vector<std::unique_ptr<MgLevel>> own;
-  DenseInv dense;  // of the coarsest level (without one: a polynomial over its whole spectrum)
+  // The cycle ends at level dlv with its dense inverse; where that is not to be
+  // used (mg_deep) or had (memory) it goes on to the last level, with the
+  // inverse `last` or else a polynomial over its whole spectrum.
+  int dlv = -1;
+  DenseInv dense, last;
 };
 
 // GPU time of one solver phase, from pairs of HIP events recorded on the
@@ -275,16 +279,22 @@ struct stokes_ctx {
   stokes::DevBuf rperm;                 // that schedule over the interior (velocity) rows
   int zblock = -1;                       // lattice planes per block of the interior row order (0: whole slab, -1: by size)
   int mg_es = 1;                        // pressure-MG lanes per row: 1 by level size, -1 timed, 0 one lane, 2-16 fixed
-  // Largest multigrid level solved by its dense inverse.  The product streams
-  // the inverse (FP32 / FP64: 4,913 rows 17 / 29 us, 8,000 rows 38 / 93 us,
-  // 10,648 rows 85 / 165 us).  mg_dense_max, where the level could coarsen
-  // further: smoothing, residuals and transfers of a level of some thousand
-  // rows and the solve below it are ten launches of 4-5 us, 36 / 40 us.
-  // The P2 pressure level of a P3/P2 pair keeps its V-cycle from 1,500 rows on
-  // (mg_dense_p2; tests pin that cycle's contraction at 1,681 and 2,197 rows).
+  // Largest multigrid level solved by its dense inverse.  mg_dense_max, where
+  // the level could coarsen further: smoothing, residuals and transfers of a
+  // level of some thousand rows and the solve below it are ten launches, the
+  // product streams the inverse.  Kernel times (the ten leave gaps of 1-2 us
+  // besides), product / cycle, right-hand sides 1, 2, 4, FP32 then FP64:
+  //   3,375 rows  12 / 29, 14 / 30, 24 / 32    18 / 31, 24 / 32, 30 / 36 us
+  //   4,913 rows  21 / 29, 27 / 31, 44 / 33    35 / 33, 45 / 33, 60 / 37 us
+  // and with eight in FP64 35 / 65 at 2,197 rows, 49 / 47 at 3,375, 114 / 51 at
+  // 4,913 (4,225 rows in 2D: 96 / 55), so those go on down from 4,000 rows
+  // (mg_deep): levels are kept to mg_dense_low rows.  The P2 pressure
+  // level of a P3/P2 pair keeps its V-cycle from there on too (tests pin that
+  // cycle's contraction at 1,681 and 2,197 rows).
   // mg_dense_last, where it cannot (an odd cell count): the polynomial over
-  // the whole spectrum is 24 launches, 100-140 / 150 us, and less exact.
-  int64_t mg_dense_max = 5000, mg_dense_p2 = 1500, mg_dense_last = 9000;
+  // the whole spectrum is 24 launches, 100-140 / 150 us, and less exact (8,000
+  // rows: product 48 / 86, polynomial 92 / 103 us of kernels).
+  int64_t mg_dense_max = 5000, mg_dense_low = 1500, mg_dense_last = 9000;
   // Bytes that forming one inverse may take, itself and its working copy
   // (< 0: half of the device memory that is free at the time).  Beyond that the
   // level is solved by the polynomial.

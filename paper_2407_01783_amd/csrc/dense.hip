@@ -181,9 +181,10 @@ __global__ __launch_bounds__(kBlock) void k_sweep_out(int64_t n, int64_t ld, int
 // or the up to 100 MB of it push the next level's rows out of the caches: its
 // 36 k-row products right after took 10.3 and 11 us, now 9.3 and 9.3), but
 // every wavefront reads all of x, NRB values per matrix entry, from the L2:
-// with one row per wavefront that is what four to eight right-hand sides wait
-// for (4,913 rows FP32, eight: 97 us, with RW = 4 76 us).  One and three gain
-// nothing from RW = 2 (20.7 and 21.0 us; 3,375 rows 16.7 and 18.6 us).
+// with one row per wavefront that is what four and more right-hand sides wait
+// for, while several rows leave a small matrix short of wavefronts (dense_rw).
+// One to three right-hand sides keep one row (4,096 rows RW = 1 / 2 / 4, FP32:
+// one 13.0 / 13.2 / 12.8 us, two 14.8 / 18.6 / 16.4).
 // ld: row pitch, a multiple of 4.
 template <typename T, int NRB, int RW>
 __global__ __launch_bounds__(kBlock) void k_dense_mv(int64_t n, int64_t ld, const T* __restrict__ Ci,
@@ -313,14 +314,39 @@ bool dense_has(const DenseInv& D) {
 template bool dense_has<float>(const DenseInv&);
 template bool dense_has<double>(const DenseInv&);
 
+// Matrix rows per wavefront from 4 values per row on, by the time of the
+// product, RW = 1 / 2 / 4 in us:
+//   rows    FP32, four     FP32, eight    FP64, four     FP64, eight
+//   1,000   6 / 7 / 10     8 / 10 / 15    7 / 8 / 12     12 / 15 / 19
+//   1,331   7 / 7 / 11     15 / 14 / 18   10 / 10 / 12   24 / 19 / 23
+//   2,744   15 / 14 / 18   35 / 27 / 30   23 / 23 / 25   64 / 54 / 41
+//   4,096   27 / 19 / 27   65 / 38 / 39   48 / 34 / 39   121 / 77 / 56
+//   5,832   47 / 33 / 45   140 / 73 / 87  108 / 59 / 66  269 / 155 / 131
+//   8,000   123 / 57 / 67  254 / 145 / 117  197 / 107 / 93  487 / 262 / 178
+// and of the velocity, 3D 3,375 rows: FP32 12 values 61 / 35 / 48, 24 values
+// 162 / 89 / 72, FP64 120 / 62 / 62, 297 / 166 / 108; 2D 2,601 rows, 16 values:
+// FP32 65 / 50 / 48, FP64 119 / 92 / 57.
+static int dense_rw(int64_t n, int W, size_t size) {
+  if (n < 1200) return 1;
+  return int64_t(n * W * size) >= (W * size >= 64 ? 130000 : 200000) ? 4 : 2;
+}
+
 template <class T>
 void dense_solve(stokes_ctx* c, const DenseInv& D, int W, const T* x, T* y) {
   const T* Ci = ops::pick<T>(D.i64, D.i32);
   auto go = [&](auto Wc) {
     constexpr int WW = decltype(Wc)::value;
-    constexpr int RW = WW >= 4 && WW <= 8 ? 4 : 1, rows = RW * kBlock / 64;
-    hipLaunchKernelGGL((k_dense_mv<T, WW, RW>), dim3((D.n + rows - 1) / rows), dim3(kBlock), 0, c->stream, D.n, D.ld,
-                       Ci, x, y);
+    auto launch = [&](auto Rc) {
+      constexpr int RW = decltype(Rc)::value, rows = RW * kBlock / 64;
+      hipLaunchKernelGGL((k_dense_mv<T, WW, RW>), dim3((D.n + rows - 1) / rows), dim3(kBlock), 0, c->stream, D.n,
+                         D.ld, Ci, x, y);
+    };
+    if constexpr (WW >= 4) {
+      const int rw = dense_rw(D.n, WW, sizeof(T));
+      if (rw == 4) return launch(std::integral_constant<int, 4>{});
+      if (rw == 2) return launch(std::integral_constant<int, 2>{});
+    }
+    launch(std::integral_constant<int, 1>{});
   };
   switch (W) {
     case 1: go(std::integral_constant<int, 1>{}); break;

@@ -192,16 +192,44 @@ void dispatch_w_mg(int W, F&& f) {
 
 }  // namespace
 
-// The coarsest level is solved by its dense inverse when it is small enough.
+// Rows of a level that is solved by its dense inverse where it cannot coarsen.
 static int64_t dense_rows(stokes_ctx* c, int64_t nrows) { return nrows <= c->mg_dense_last ? nrows : 0; }
 
+// Eight FP64 right-hand sides: from some 4,000 rows on the cycle below the
+// dense level is the faster one.
 template <class T>
-void mg_ready(stokes_ctx* c, MgHier& H) {
-  if (H.lv.empty()) return;
-  dense_ready<T>(c, *H.lv.back().S, H.lv.back().v64->as<const double>(), H.dense);
+static bool mg_deep(const MgHier& H, int nrb) {
+  return nrb * sizeof(T) >= 64 && H.dlv + 1 < static_cast<int>(H.lv.size()) && H.dense.n > 4000;
 }
-template void mg_ready<double>(stokes_ctx*, MgHier&);
-template void mg_ready<float>(stokes_ctx*, MgHier&);
+
+// Choose the dense level of a built hierarchy: the first one within
+// mg_dense_max (a P2 pressure level: mg_dense_low) rows, or the last one.
+static void dense_levels(stokes_ctx* c, MgHier& H) {
+  const int nlev = static_cast<int>(H.lv.size());
+  H.dlv = -1;
+  H.dense.reset(0);
+  H.last.reset(0);
+  for (int l = 0; l < nlev && H.dlv < 0; ++l) {
+    const int64_t nr = H.lv[l].S->nrows;
+    const bool p2 = c->mesh.order == 3 && l == 0;
+    if (l == nlev - 1 ? dense_rows(c, nr) > 0 : nr <= (p2 ? c->mg_dense_low : c->mg_dense_max)) H.dlv = l;
+  }
+  if (H.dlv >= 0) H.dense.reset(H.lv[H.dlv].S->nrows);
+  if (H.dlv >= 0 && H.dlv < nlev - 1) H.last.reset(dense_rows(c, H.lv[nlev - 1].S->nrows));
+}
+
+template <class T>
+void mg_ready(stokes_ctx* c, MgHier& H, int nrb) {
+  if (H.dlv < 0) return;
+  const MgHier::View &V = H.lv[H.dlv], &L = H.lv.back();
+  if (!mg_deep<T>(H, nrb)) {
+    dense_ready<T>(c, *V.S, V.v64->as<const double>(), H.dense);
+    if (dense_has<T>(H.dense)) return;
+  }
+  dense_ready<T>(c, *L.S, L.v64->as<const double>(), H.last);
+}
+template void mg_ready<double>(stokes_ctx*, MgHier&, int);
+template void mg_ready<float>(stokes_ctx*, MgHier&, int);
 
 // Entry-split lanes per level (Sell::es).  The coarse levels have a few
 // thousand rows of a two-ring stencil, where one lane per row leaves the chip
@@ -280,9 +308,7 @@ void build_mg(stokes_ctx* c) {
   const int D = fm.dim;
   int n = fm.order == 3 ? 2 * fm.n : fm.n;  // lattice intervals per side of the pressure nodes
   H.lv.push_back({&c->sQ, &c->XQ64, &c->XQ32, &c->dXQ64, &c->dXQ32, &c->bXQ_smooth, &c->bXQ, n});
-  // coarsen while the current level is too large for the dense coarse solve
-  auto dense_max = [&] { return fm.order == 3 && n == 2 * fm.n ? c->mg_dense_p2 : c->mg_dense_max; };
-  while (n % 2 == 0 && n > 2 && ipow(n + 1, D) > dense_max()) {
+  while (n % 2 == 0 && n > 2 && ipow(n + 1, D) > c->mg_dense_low) {
     n /= 2;
     const int stride = fm.n / n;  // mesh vertices per coarse cell side
     auto L = std::make_unique<MgLevel>();
@@ -304,7 +330,7 @@ void build_mg(stokes_ctx* c) {
     H.lv.push_back({&L->S, &L->v64, &L->v32, &L->d64, &L->d32, &L->bs, &L->bf, n});
     H.own.push_back(std::move(L));
   }
-  H.dense.reset(dense_rows(c, H.lv.back().S->nrows));
+  dense_levels(c, H);
   // The Galerkin hierarchy of B_I Lambda_V^-1 B_I^T + M_Q.  On the P2
   // pressure of a P3/P2 pair that operator is close to the P2 mass matrix,
   // whose low-energy modes include non-smooth ones (vertex and edge values
@@ -314,11 +340,10 @@ void build_mg(stokes_ctx* c) {
   // stays symmetric positive definite and is the better preconditioner.
   c->mgx.lv.clear();
   c->mgx.own.clear();
-  c->mgx.dense.reset(0);
   if (fm.order != 3 || c->mgx_p3) {
     assemble_galerkin(c, c->mgx);
-    c->mgx.dense.reset(dense_rows(c, c->mgx.lv.back().S->nrows));
   }
+  dense_levels(c, c->mgx);
   tune_levels(c, c->mgq);
   tune_levels(c, c->mgx);
 }
@@ -381,9 +406,13 @@ void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, bool f
       std::swap(da, db);
     }
   };
-  if (lv == nlev - 1) {  // coarsest: dense inverse, or a polynomial over the whole spectrum
-    if (dense_has<T>(H.dense)) {
-      dense_solve<T>(c, H.dense, nrb, r, e);
+  if (lv == H.dlv && !mg_deep<T>(H, nrb) && dense_has<T>(H.dense)) {
+    dense_solve<T>(c, H.dense, nrb, r, e);
+    return;
+  }
+  if (lv == nlev - 1) {  // dense inverse, or a polynomial over the whole spectrum
+    if (dense_has<T>(H.last)) {
+      dense_solve<T>(c, H.last, nrb, r, e);
     } else {
       cheb(bf, c->mg_coarse_degree, r, e, 0);
     }

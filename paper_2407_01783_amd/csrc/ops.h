@@ -23,7 +23,7 @@ void assemble_galerkin(stokes_ctx* c, MgHier& H);
 // half-precision roundings: for methods that take any linear preconditioner
 // (FGMRES), not for conjugate gradients.
 template <class T>
-void mg_ready(stokes_ctx* c, MgHier& H);  // before the first cycle in T (dense_ready)
+void mg_ready(stokes_ctx* c, MgHier& H, int nrb);  // before the first cycle in T at this width (dense_ready)
 template <class T>
 void mg_vcycle(stokes_ctx* c, const MgHier& H, int nrb, const T* r, T* e, bool flexible = false, int level = 0);
 // Dense inverse of a coarsest level (dense.hip).  dense_ready: forms it in T

@@ -454,7 +454,7 @@ class Engine {
     // V-cycle of eps M_Q + L_Q
     MgHier& H =
         (o_.schur_pc == STOKES_CC_LUMPED && c_->use_mgx && !c_->mgx.lv.empty()) ? c_->mgx : c_->mgq;
-    mg_ready<T>(c_, H);
+    mg_ready<T>(c_, H, nrb_);
     pc.apply = [this, &H](const T* r, T* z) { mg_vcycle<T>(c_, H, nrb_, r, z); };
     if (o_.inner_mode == STOKES_INNER_FIXED) {
       mg_vcycle<T>(c_, H, nrb_, b, x, flexible);
