@@ -9,16 +9,29 @@ namespace ops {
 namespace {
 
 // Lanes per pressure row: the fewest of 1, 2, 4, 8 that give the chip about
-// 7 * 2^14 lanes (7 wavefronts per CU).  Timed on 3D meshes of 9 to 64 cells:
-// at 35,937 rows E = 1 / 2 / 4 / 8 takes 17.0 / 15.1 / 14.6 / 16.2 us, at
-// 68,921 rows 21.8 / 20.2 / 21.8 / 22.2 us and at 117,649 rows 23.9 / 27.6 /
-// 30.9 / 32.0 us (FP32), where split rows only fragment the slot loads.
-// Eight FP64 right-hand sides gather 192-byte segments and take four lanes on
-// any mesh (274,625 rows: 669 us with one lane, 473 with two, 463 with four).
-int b_lanes(const Sell& S, int nrb, bool f64) {
+// 6 * 2^14 lanes (6 wavefronts per CU).  E = 1 / 2 / 4 / 8 in us, P2/P1 in 3D,
+// one right-hand side:
+//   35,937 rows FP32 26 / 15 / 15 / 16, FP64 30 / 27 / 25 / 28
+//   50,653 rows      27 / 16 / 18 / 18       32 / 30 / 32 / 33
+//   91,125 rows      32 / 22 / 25 / 27       53 / 46 / 47 / 53
+//   117,649 rows     35 / 29 / 32 / 33       57 / 57 / 59 / 65
+// Wider rows of u, gathered in pieces of 24 D bytes and more, differ:
+//   * eight FP64 right-hand sides take four lanes on any mesh, two on P3/P2
+//     pairs (P2/P1, 274,625 rows 668 / 472 / 463 / 471; P3/P2, 50,653 rows 174 /
+//     145 / 203 / 170, 117,649 rows 393 / 368 / 388 / 351);
+//   * 32 bytes per component (eight FP32, four FP64) take eight in 3D below
+//     5 * 2^14 rows (35,937 rows 37 / 42 / 37 / 32 and 43 / 52 / 42 / 39,
+//     68,921 rows 73 / 68 / 59 / 54 and 95 / 79 / 68 / 68; against them 50,653
+//     rows 40 / 44 / 47 / 42 and 48 / 54 / 55 / 53), one in 2D from 2^16 on
+//     (66,049 rows 14 / 16 / 15 / 17 and 15 / 17 / 15 / 17).
+int b_lanes(const Sell& S, int dim, bool p3, int nrb, size_t size) {
+  const int64_t rows = S.nrows;
   int e = 1;
-  while (e < 8 && S.nrows * e < 7 * (int64_t(1) << 14)) e *= 2;
-  return f64 && nrb == 8 ? std::max(e, 4) : e;
+  while (e < 8 && rows * e < 6 * (int64_t(1) << 14)) e *= 2;
+  if (nrb * size == 64) return std::max(e, p3 ? 2 : 4);
+  if (nrb * size == 32 && dim == 3 && rows < 5 * (int64_t(1) << 14)) return 8;
+  if (nrb * size == 32 && dim == 2 && rows >= (int64_t(1) << 16)) return 1;
+  return e;
 }
 
 }  // namespace
@@ -27,7 +40,7 @@ template <class T>
 void Bmul(stokes_ctx* c, int nrb, const T* u, T* p, T a, const T* pin, T b) {
   const Sell& S = c->sB;
   const T* vals = pick<T>(c->B64, c->B32);
-  const int lanes = b_lanes(S, nrb, std::is_same<T, double>::value);
+  const int lanes = b_lanes(S, c->dim, c->mesh.order == 3, nrb, sizeof(T));
   dispatch_dn(c->dim, nrb, [&](auto Dc, auto Nc) {
     constexpr int D = decltype(Dc)::value, N = decltype(Nc)::value;
     auto go = [&](auto Ec) {
