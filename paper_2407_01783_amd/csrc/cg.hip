@@ -13,7 +13,7 @@ void spmv_grid(stokes_ctx* c, int64_t nrows, const Sell* S, bool blocks, int W, 
   if (blocks) {  // one lane per row in any case: the widths need not be those of split_lg
     lg = W <= 3 ? dot_rows(nrows, W, split_rows(nrows, W)) : 0;
   } else {
-    lg = S ? split_lg_dot(nrows, G, W / G) : 0;
+    lg = S ? split_lg_dot(c, *S, G, W / G) : 0;
   }
   nb = lg ? grid_rows(nrows, G, lg) : grid_for(nrows * G);
 }
@@ -27,7 +27,7 @@ CgPlan cg_plan(stokes_ctx* c, int64_t nrows, const Sell* S, bool blocks, const S
   int G, lg;
   spmv_grid<T>(c, nrows, S, blocks, W, G, lg, p.nsig);
   p.nrr = grid_for(nrows * lanes_rows(c, nrows, W, f32));
-  p.nrho = cheb_dot_grid(pcS.nrows, lanes_op(c, &pcS, W, f32), W, lg);
+  p.nrho = cheb_dot_grid(c, pcS, lanes_op(c, &pcS, W, f32), W, lg);
   p.fold = W <= kFoldWidth && int64_t(std::max(std::max(p.nsig, p.nrr), p.nrho)) * W <= kFoldMax;
   return p;
 }

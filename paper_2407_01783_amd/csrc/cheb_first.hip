@@ -24,7 +24,7 @@ void cheb_first_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, const T
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int lg = split_lg(c, S, GG, WW / GG);
       const int nb = grid_rows(S.nrows, GG, lg);
       with_split<GG, WW / GG>(lg, [&](auto SPc) {
         constexpr bool SP = decltype(SPc)::value;
@@ -92,7 +92,7 @@ void cheb_first_hb(stokes_ctx* c, int W, const float* r, const float* dinv, floa
     wp = bf_width<WW>();
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int lg = split_lg(c, S, GG, WW / GG);
       const int nb = grid_rows(S.nrows, GG, lg);
       il = c->vel_il && c->AD16i.p;  // the eight-slot interleaved copies
       with_split<GG, WW / GG>(lg, [&](auto SPc) {

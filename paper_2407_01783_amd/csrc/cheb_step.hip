@@ -23,7 +23,7 @@ void cheb_step_hb(stokes_ctx* c, int W, const uint16_t* q, uint16_t* qn, const f
     wp = bf_width<WW>();
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int lg = split_lg(c, S, GG, WW / GG);
       const int nb = grid_rows(S.nrows, GG, lg);
       with_split<GG, WW / GG>(lg, [&](auto SPc) {
         constexpr bool SP = decltype(SPc)::value;
@@ -101,7 +101,7 @@ void cheb_step_hs(stokes_ctx* c, const Sell& S, const _Float16* vals, float ms, 
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int lg = split_lg(c, S, GG, WW / GG);
       with_split<GG, WW / GG>(lg, [&](auto SPc) {
         hipLaunchKernelGGL((k_cheb_step<float, WW, 0, GG, _Float16, decltype(SPc)::value>),
                            dim3(grid_rows(S.nrows, GG, lg)), dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), vals, ms, d,
@@ -131,8 +131,8 @@ void cheb_step(stokes_ctx* c, const Sell& S, const T* vals, int W, const T* d, T
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      int lg = split_lg(S.nrows, GG, WW / GG);
-      const int nb = rvec ? cheb_dot_grid(S.nrows, GG, WW, lg) : grid_rows(S.nrows, GG, lg);
+      int lg = split_lg(c, S, GG, WW / GG);
+      const int nb = rvec ? cheb_dot_grid(c, S, GG, WW, lg) : grid_rows(S.nrows, GG, lg);
       double* sums = rvec && rho_mode == RHO_FOLDED ? rho_partials(c) : partials(c);
       with_split<GG, WW / GG>(lg, [&](auto SPc) {
         constexpr bool SP = decltype(SPc)::value;

@@ -71,10 +71,21 @@ inline int grid_rows(int64_t rows, int G, int lg) {
 // that is timed per context and must not change the sums.  The lines lie where
 // the card stops being short of wavefronts (2^14 fill it, at 64 rows each), by
 // the time of one product at lg = 0 / 1 / 2, in us:
-//   width 1   16 k rows: half product 6.1 / 4.9 / 4.0; 36 k: 6.0 / 6.1 / 5.2,
-//             first step 9.6 / 8.1 / 6.6; 69 k: 7.4 / 7.5 / 6.6, first step
-//             9.8 / 8.8 / 9.0; 119 k (200 entries a row): 49 / 48 / 43, first
-//             step 70 / 66 / 61; 276 k: 12.3 / 14.2 / 15.2
+//   width 1, rows of 24 slots or more (two-ring levels, P2 pressure levels):
+//             two-ring P1 in 3D (65), FP64 product 36 k 8.5 / 8.0 / 6.8; 69 k
+//             14.0 / 12.2 / 10.4; 91 k 15.4 / 13.8 / 12.9; 118 k 17.1 / 16.8 /
+//             16.1; 185 k 23.9 / 22.8 / 23.3; FP32 118 k 8.0 / 8.3 / 8.3;
+//             P2 level in 3D (200), half, 118 k: 51 / 49 / 45
+//   width 1, short rows, 3D (M_Q, L_Q and their levels: 15): FP32 first and
+//             later step 36 k 5.6 / 5.4 / 4.8; 55 k 4.8 / 4.4 / 4.4, 4.4 / 4.2 /
+//             4.3; 74 k 5.1 / 4.8 / 5.8, 4.6 / 4.5 / 4.6; 97 k 5.1 / 4.9 / 6.2,
+//             4.5 / 4.5 / 4.9; 125 k 5.0 / 5.0 / 6.4, 4.6 / 4.8 / 5.6; FP64 later
+//             step 55 k 4.9 / 4.9 / 4.8; 74 k 5.7 / 6.4 / 6.5; 97 k 5.5 / 5.9 /
+//             6.8; 125 k 6.4 / 6.6 / 7.7
+//   width 1, short rows, 2D: L_Q (7), FP64 later step 33 k 3.9 / 4.2 / 4.4,
+//             49 k 3.9 / 4.2 / 4.4; first step 26 k 5.1 / 4.3 / 4.5; two-ring
+//             (19), FP64 first step 26 k 6.2 / 5.4 / 5.0; 40 k 6.2 / 6.1 / 5.8;
+//             49 k 5.5 / 5.5 / 5.4, later 4.6 / 4.9 / 5.0; 103 k 8.8 / 9.6 / 11.0
 //   width 3   68 k rows FP32 step best at 2; 104 k: bfloat16 step
 //             12.1 / 8.5 / 8.9, first step 11.7 / 8.4 / 8.3, K_gamma product
 //             11.6 / 9.1 / 9.0, B^T 7.8 / 6.8 / 6.4; 251 k: 14.2 / 12.7 /
@@ -86,7 +97,14 @@ inline int split_rows(int64_t rows, int wg) {
   if (rows < (int64_t(1) << 17) && rows * wg < (int64_t(1) << 18)) return 2;
   return wg > 1 && rows < (int64_t(1) << 19) ? 1 : 0;
 }
-inline int split_lg(int64_t rows, int G, int wg) { return G == 1 && split_width(wg) ? split_rows(rows, wg) : 0; }
+inline int split_lg(stokes_ctx* c, const Sell& S, int G, int wg) {
+  if (G != 1 || !split_width(wg)) return 0;
+  const int64_t rows = S.nrows;
+  if (wg > 1 || S.nnz_pad >= 24 * rows) return split_rows(rows, wg);
+  if (c->dim == 2 && S.nnz_pad < 10 * rows) return rows < 7 * (int64_t(1) << 12) ? 2 : 0;
+  if (rows < 3 * (int64_t(1) << 14)) return 2;
+  return c->dim == 3 && rows < (int64_t(1) << 16) ? 1 : 0;
+}
 
 // Partial sums (workgroups times width) up to which the kernels that use a CG
 // scalar add them up themselves (cg_plan in cg.hip): every wavefront reads all
@@ -105,12 +123,14 @@ inline int dot_rows(int64_t rows, int W, int lg) {
   while (lg > 0 && grid_rows(rows, 1, lg) > kMaxBlocks) --lg;
   return lg;
 }
-inline int split_lg_dot(int64_t rows, int G, int wg) { return dot_rows(rows, G * wg, split_lg(rows, G, wg)); }
+inline int split_lg_dot(stokes_ctx* c, const Sell& S, int G, int wg) {
+  return dot_rows(S.nrows, G * wg, split_lg(c, S, G, wg));
+}
 
 // Workgroups (and lg) of a Chebyshev step that ends in a sum.
-inline int cheb_dot_grid(int64_t rows, int G, int W, int& lg) {
-  lg = split_lg_dot(rows, G, W / G);
-  return lg ? grid_rows(rows, G, lg) : grid_for(rows * G);
+inline int cheb_dot_grid(stokes_ctx* c, const Sell& S, int G, int W, int& lg) {
+  lg = split_lg_dot(c, S, G, W / G);
+  return lg ? grid_rows(S.nrows, G, lg) : grid_for(S.nrows * G);
 }
 
 // f(SP): the shared-slice variant of a kernel where lg > 0.

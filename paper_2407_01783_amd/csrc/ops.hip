@@ -106,7 +106,7 @@ void spmv_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, int W, const 
       if (&S == &c->sA && c->vel_il && c->A32i.p && (const void*)vals == c->A32.p) {
         with_g<WW>(G, [&](auto Gc) {
           constexpr int GG = decltype(Gc)::value;
-          const int lg = split_lg(S.nrows, GG, WW / GG);
+          const int lg = split_lg(c, S, GG, WW / GG);
           with_split<GG, WW / GG>(lg, [&](auto SPc) {
             hipLaunchKernelGGL((k_spmv<T, WW, GG, TM, true, decltype(SPc)::value>), dim3(grid_rows(S.nrows, GG, lg)),
                                dim3(kBlock), 0, c->stream, S.nrows, vel_il_idx(c, WW, il_width<float>()),
@@ -125,7 +125,7 @@ void spmv_impl(stokes_ctx* c, const Sell& S, const TM* vals, T ms, int W, const 
       return;
     with_g<WW>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int lg = split_lg(S.nrows, GG, WW / GG);
+      const int lg = split_lg(c, S, GG, WW / GG);
       with_split<GG, WW / GG>(lg, [&](auto SPc) {
         hipLaunchKernelGGL((k_spmv<T, WW, GG, TM, false, decltype(SPc)::value>), dim3(grid_rows(S.nrows, GG, lg)),
                            dim3(kBlock), 0, c->stream, S.nrows, S.idx(WW), vals, x, y, (T)(a * ms), yin, b, lg);
@@ -157,7 +157,7 @@ void Btmul(stokes_ctx* c, int nrb, const T* p, const T* scale, T* u, T a, const 
     constexpr int D = decltype(Dc)::value, N = decltype(Nc)::value;
     with_g<D * N>(G, [&](auto Gc) {
       constexpr int GG = decltype(Gc)::value;
-      const int lg = split_lg(S.nrows, GG, D * N / GG);
+      const int lg = split_lg(c, S, GG, D * N / GG);
       with_split<GG, D * N / GG>(lg, [&](auto SPc) {
         hipLaunchKernelGGL((k_Bt<T, D, N, GG, decltype(SPc)::value>), dim3(grid_rows(S.nrows, GG, lg)), dim3(kBlock), 0,
                            c->stream, S.nrows, S.idx(D * N), btvals<T>(c).template as<T>(), p, scale, u, a, uin, b,
