@@ -74,8 +74,8 @@ enum FinKind { FIN_STORE = 0, FIN_ALPHA = 1, FIN_RR = 2, FIN_RR_RHO = 3, FIN_RHO
 //   FIN_STORE   res[s] = total of slot s
 //   FIN_ALPHA   sigma = p.q per system, alpha = rho / sigma (0 if inactive)
 //   FIN_RR      rr = r.r per system, deactivate converged systems
-//   FIN_RR_RHO  FIN_RR and rho = r.z (slots W..2W-1), beta = rho / rho_old
-//   FIN_RHO     rho = r.z, beta = rho / rho_old (0 when `first`)
+//   FIN_RR_RHO  FIN_RR and rho = r.z (slots W..2W-1), beta = rho / the last rho
+//   FIN_RHO     rho = r.z, beta = rho / the last rho (0 when `first`)
 template <int NS>
 __global__ __launch_bounds__(kBlock) void k_finish(const double* __restrict__ partials, int nblocks, int kind, int W,
                                                    Scalars* sc, int cps, int nsys, int first, double* res) {
@@ -972,6 +972,11 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step_es(int64_t nrows, SellIdx 
   }
 }
 
+// the row of the strain operator's block product (further down)
+template <typename T, int D, int NRB>
+__device__ void sell_row_blk(const SellIdx& ix, const T* __restrict__ vals, const T* __restrict__ x, int64_t row,
+                             T (&acc)[D * NRB], RowPart part = {});
+
 // CG direction step with the product folded in:
 //   q = S z (+ extra) + beta q,  p = z + beta p,  sigma = p . q  -> alpha
 // BD = D: vals hold the D x D blocks of the strain operator.  With the blocks
@@ -1751,7 +1756,7 @@ __device__ __forceinline__ void sell_row_blk_impl(const SellIdx& ix, const Slice
 
 template <typename T, int D, int NRB>
 __device__ __forceinline__ void sell_row_blk(const SellIdx& ix, const T* __restrict__ vals, const T* __restrict__ x,
-                                             int64_t row, T (&acc)[D * NRB], RowPart part = {}) {
+                                             int64_t row, T (&acc)[D * NRB], RowPart part) {
   const SliceRef rf = slice_ref(ix, row);
   if (rf.af) sell_row_blk_impl<T, D, NRB, 2>(ix, rf, vals, x, row, part, acc);
   else if (rf.pk) sell_row_blk_impl<T, D, NRB, 1>(ix, rf, vals, x, row, part, acc);
