@@ -474,11 +474,12 @@ bool small_resident(const Sell& S, int W, size_t lds) {
 // Which systems run in one launch: those whose matrix stays in the LDS, and
 // those that stream at most 1.5 MB per iteration (one compute unit draws some
 // 60 bytes a cycle from the L2; a 4-step preconditioner and the operator) and
-// whose gathered vectors fit.  Whole solves, FP64 / FP32, launches before and
-// one launch now: 225 rows 25 -> 10 ms, 961 rows 42 -> 22 ms, 2,209 rows (1.2
-// MB) 61 -> 47 ms; 3D 1,331 rows (1.7 MB) 24 -> 20 ms, 2,197 rows (2.7 MB) 25
-// -> 27 ms; FP32 3,969 rows (1.4 MB) 15 -> 10 ms, 9,025 rows (3.2 MB) 22 -> 26
-// ms.
+// whose gathered vectors fit.  Whole solves, FP64 / FP32, launches with their
+// scalars formed where they are used and one launch: 225 rows 25 -> 11 / 25 ->
+// 11 ms, 961 rows 48 -> 24 / 50 -> 21, 2,209 rows (1.2 MB) 63 -> 53 / 66 -> 39,
+// FP32 3,025 rows 78 -> 53; 3D 343 rows 21 -> 15, FP32 729 rows 23 -> 17.  Past
+// the line, when it was drawn: FP64 2,197 rows in 3D (2.7 MB) 25 -> 27, FP32
+// 9,025 rows (3.2 MB) 22 -> 26 ms.
 template <class T>
 bool pcg_small_fits(stokes_ctx* c, int W, int degree) {
   const Sell& S = c->sA;
@@ -488,6 +489,11 @@ bool pcg_small_fits(stokes_ctx* c, int W, int degree) {
   const double op = c->strain ? double(S.nnz_pad) * (sizeof(T) * W * (W + 1) / 2 + 4.0) : step;
   if (small_resident<T>(S, W, c->lds_bytes)) return !c->strain || op <= 1.5e6;
   return (degree - 1) * step + op <= 1.5e6;
+}
+
+template <class T>
+bool pcg_small_resident(stokes_ctx* c, int W) {
+  return small_resident<T>(c->sA, W, c->lds_bytes);
 }
 
 template <class T>
@@ -534,7 +540,8 @@ void pcg_small(stokes_ctx* c, int W, int cps, int degree, T thinv, const double*
 }
 
 #define INST(T)                                                                                                  \
-  template bool pcg_small_fits<T>(stokes_ctx*, int, int);                                                           \
+  template bool pcg_small_fits<T>(stokes_ctx*, int, int);                                                        \
+  template bool pcg_small_resident<T>(stokes_ctx*, int);                                                         \
   template void pcg_small<T>(stokes_ctx*, int, int, int, T, const double*, const double*, double, int, const T*, \
                              T*, T*, T*, T*, T*, T*, Scalars*);
 INST(float)

@@ -212,7 +212,8 @@ class Engine {
     bool mean_free = false;  // apply: on pressures, for an operator that is singular on constants
   };
 
-  // Solve op x = b per system to ||r|| <= rtol ||b||; returns iterations.
+  // Solve op x = b per system to ||r|| <= rtol ||b||; returns the iterations
+  // that ran (in launches of their own: up to the host's next look).
   // graph = true replays the iteration body as a captured graph (worth it for
   // the many short kernels of the pressure solve).
   // fixed > 0 runs exactly that many iterations without convergence checks.
@@ -235,15 +236,16 @@ class Engine {
       sync_scalars(sc_index);
       const int run = c_->h_scal->iters;
       check_breakdown(tag, run, nsys);
-      // counted as the launches below count: the operator and each step of the
-      // polynomial once per iteration, host checks every cg_check_every
-      const double vec = double(n) * sizeof(T);
-      ops::count_bytes(c_, (run + 1.0) * (pc.degree - 1) * (ops::op_bytes(c_->sA, sizeof(T)) + 6 * vec) +
-                               run * (ops::op_bytes(c_->sA, sizeof(T)) * (c_->strain ? 0.5 * D_ * (D_ + 1) : 1.0) +
-                                      13 * vec));
-      if (fixed > 0) return fixed;
-      const int every = std::max(1, c_->cg_check_every);
-      return std::min(maxit, (run + every - 1) / every * every);
+      log_pcg(tag, run, nsys);
+      // the operator and each step of the polynomial once per iteration, or
+      // once per solve where they stay on chip (the strain blocks do not)
+      const double vec = double(n) * sizeof(T), A = ops::op_bytes(c_->sA, sizeof(T));
+      const double blk = c_->strain ? A * 0.5 * D_ * (D_ + 1) : 0;
+      if (ops::pcg_small_resident<T>(c_, W))
+        ops::count_bytes(c_, A + run * blk + 3 * vec);
+      else
+        ops::count_bytes(c_, (run + 1.0) * (pc.degree - 1) * (A + 6 * vec) + run * ((c_->strain ? blk : A) + 13 * vec));
+      return run;
     }
     T* t = (op.apply || op.extra) ? buf(tag + "_t", n) : nullptr;
     ops::zero_dev(c_, x, n * sizeof(T));
@@ -341,12 +343,7 @@ class Engine {
       bool any = false;
       for (int s = 0; s < nsys; ++s) any = any || h.active[s];
       if (!any || it >= maxit) {
-        if (log_level() >= 2) {
-          double worst = 0;
-          for (int s2 = 0; s2 < nsys; ++s2)
-            if (h.bb[s2] > 0) worst = std::max(worst, std::sqrt(h.rr[s2] / h.bb[s2]));
-          std::fprintf(stderr, "[stokes]   pcg %s: %d its, max rel res %.3e\n", tag.c_str(), it, worst);
-        }
+        log_pcg(tag, it, nsys);
         break;
       }
       const int k = std::min(every, maxit - it);
@@ -357,6 +354,15 @@ class Engine {
       it += k;
     }
     return it;
+  }
+
+  void log_pcg(const std::string& tag, int it, int nsys) {
+    if (log_level() < 2) return;
+    const Scalars& h = *c_->h_scal;
+    double worst = 0;
+    for (int s = 0; s < nsys; ++s)
+      if (h.bb[s] > 0) worst = std::max(worst, std::sqrt(h.rr[s] / h.bb[s]));
+    std::fprintf(stderr, "[stokes]   pcg %s: %d its, max rel res %.3e\n", tag.c_str(), it, worst);
   }
 
   void check_breakdown(const std::string& tag, int it, int nsys) {
