@@ -198,8 +198,6 @@ void cheb_step_h(stokes_ctx* c, int W, const float* q, float* qn, const float* r
 template <class T>
 bool pcg_small_fits(stokes_ctx* c, int W, int degree);
 template <class T>
-bool pcg_small_resident(stokes_ctx* c, int W);  // the matrix is read once per solve
-template <class T>
 void pcg_small(stokes_ctx* c, int W, int cps, int degree, T thinv, const double* c1, const double* c2, double rtol,
                int maxit, const T* b, T* x, T* r, T* p, T* q, T* res, T* z, Scalars* sc);
 

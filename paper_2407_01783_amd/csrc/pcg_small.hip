@@ -492,11 +492,6 @@ bool pcg_small_fits(stokes_ctx* c, int W, int degree) {
 }
 
 template <class T>
-bool pcg_small_resident(stokes_ctx* c, int W) {
-  return small_resident<T>(c->sA, W, c->lds_bytes);
-}
-
-template <class T>
 void pcg_small(stokes_ctx* c, int W, int cps, int degree, T thinv, const double* c1, const double* c2, double rtol,
                int maxit, const T* b, T* x, T* r, T* p, T* q, T* res, T* z, Scalars* sc) {
   const Sell& S = c->sA;
@@ -541,7 +536,6 @@ void pcg_small(stokes_ctx* c, int W, int cps, int degree, T thinv, const double*
 
 #define INST(T)                                                                                                  \
   template bool pcg_small_fits<T>(stokes_ctx*, int, int);                                                        \
-  template bool pcg_small_resident<T>(stokes_ctx*, int);                                                         \
   template void pcg_small<T>(stokes_ctx*, int, int, int, T, const double*, const double*, double, int, const T*, \
                              T*, T*, T*, T*, T*, T*, Scalars*);
 INST(float)

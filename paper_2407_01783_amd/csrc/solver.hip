@@ -237,14 +237,12 @@ class Engine {
       const int run = c_->h_scal->iters;
       check_breakdown(tag, run, nsys);
       log_pcg(tag, run, nsys);
-      // the operator and each step of the polynomial once per iteration, or
-      // once per solve where they stay on chip (the strain blocks do not)
-      const double vec = double(n) * sizeof(T), A = ops::op_bytes(c_->sA, sizeof(T));
-      const double blk = c_->strain ? A * 0.5 * D_ * (D_ + 1) : 0;
-      if (ops::pcg_small_resident<T>(c_, W))
-        ops::count_bytes(c_, A + run * blk + 3 * vec);
-      else
-        ops::count_bytes(c_, (run + 1.0) * (pc.degree - 1) * (A + 6 * vec) + run * ((c_->strain ? blk : A) + 13 * vec));
+      // counted as the launches below count: the operator and each step of the
+      // polynomial once per iteration, wherever the values come from
+      const double vec = double(n) * sizeof(T);
+      ops::count_bytes(c_, (run + 1.0) * (pc.degree - 1) * (ops::op_bytes(c_->sA, sizeof(T)) + 6 * vec) +
+                               run * (ops::op_bytes(c_->sA, sizeof(T)) * (c_->strain ? 0.5 * D_ * (D_ + 1) : 1.0) +
+                                      13 * vec));
       return run;
     }
     T* t = (op.apply || op.extra) ? buf(tag + "_t", n) : nullptr;
