@@ -498,8 +498,12 @@ void build_vmg(stokes_ctx* c) {
     assemble_p2_level(c, m, *L);
     // lanes per row: coarse levels have at most an eighth of the fine rows, too
     // few to hide a row's chain of gathers behind other rows.  FP32, 3D, one
-    // right-hand side, one lane / 4 / 8 per row: 29,791 rows 13.2 / 8.5 / 11.3
-    // us per product, 3,375 rows 12.2 / 6.2 / 5.5 us.
+    // right-hand side, one lane (a slice not shared) / 4 / 8 per row: 29,791 rows
+    // 13.2 / 8.5 / 11.3 us per product, 3,375 rows 12.2 / 6.2 / 5.5 us.  Kernels
+    // of a whole cycle with one lane (slices shared where the width allows it)
+    // / 4 / 8 on every coarse level, FP32: 3D 32 cells 181 / 189 / 209 us, 64 cells
+    // 828 / 897 / 988, with two right-hand sides 313 / 269 / 284 and 1,417 / 1,393 /
+    // 1,474; 2D 128 cells 104 / 97 / 94, 256 cells 173 / 163 / 189.
     L->S.es = L->S.nrows < (int64_t(1) << 14) ? 8 : 4;
     HostCsr P, R;
     std::vector<double> pv;

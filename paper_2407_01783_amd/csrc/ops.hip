@@ -207,7 +207,8 @@ void momentum(stokes_ctx* c, int nrb, const T* u, const T* p, const T* extra, T*
   }
   // Eight FP64 right-hand sides in 3D: the product of A wants several lanes per
   // row and that of B^T one, and a kernel for both has to take one number
-  // (2,048,383 rows: 1,815 us with four; apart 510 and 1,064 us).
+  // (29,791 rows 59 us with four, apart 11 and 21; 357,911 rows 317, apart 68 and
+  // 169; 2,048,383 rows 1,815, apart 510 and 1,064).
   if (c->dim * nrb == 24 && std::is_same<T, double>::value && !extra) {
     Btmul<T>(c, nrb, p, nullptr, y, -sgn, yin, yin ? (T)1 : (T)0, nullptr);
     spmv<T>(c, c->sA, avals<T>(c).template as<T>(), c->dim * nrb, u, y, sgn, y, (T)1);
